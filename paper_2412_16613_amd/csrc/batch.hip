@@ -11,7 +11,7 @@
 // order in which waves take items changes nothing in the results.  Every
 // wave leaves the loop once the queue counter passes the item count.
 
-#include "wm_device.h"
+#include "lanes_device.h"
 
 namespace bwg {
 
@@ -78,12 +78,21 @@ __device__ __noinline__ void wm_word_bucket(const WmArgs *ap, uint64_t w, uint64
     wm_word<NB, BC, -1, -1>(a, w);
 }
 
+template <int NQ>
 __device__ __noinline__ void wm_lanes_item(const WmArgs *ap, uint64_t w, uint32_t *sq,
                                            uint64_t max_events)
 {
     const WmArgs a = uniform_args(ap, max_events);
-    wm_lanes(a, w, sq);
+    if (a.fa >= 0 && a.fi >= 0 && a.cu < 65536u)
+        wm_lanes<NQ, FrankReplica<true>>(a, w, sq);
+    else
+        wm_lanes<NQ, FrankReplica<false>>(a, w, sq);
 }
+
+#define BWG_LANES_CASE(nq)                                                          \
+    case nq:                                                                        \
+        wm_lanes_item<nq>(&ens[k].a, w, sq_dyn + half * kLanesHalfWords, max_events); \
+        break;
 
 #define BWG_PERSIST_CASE(id, nb, bc)        \
     case id:                                \
@@ -107,9 +116,14 @@ __global__ __launch_bounds__(64, 2) void wm_persistent_kernel(const BatchEns *en
         const BatchItem bi = items[it];
         if (bi.ens & BATCH_ITEM_LANES) {
             const int half = threadIdx.x >> 5;
-            wm_lanes_item(&ens[bi.ens & ~BATCH_ITEM_LANES].a, (uint64_t)bi.word0 + half,
-                          sq_dyn + half * kLanesHalfWords,
-                          max_events);
+            const uint32_t k = bi.ens & ~BATCH_ITEM_LANES;
+            const uint64_t w = (uint64_t)bi.word0 + half;
+            switch ((uni32((uint32_t)ens[k].a.B) + 3) / 4) {
+                BWG_LANES_CASE(1) BWG_LANES_CASE(2) BWG_LANES_CASE(3) BWG_LANES_CASE(4)
+                BWG_LANES_CASE(5) BWG_LANES_CASE(6) BWG_LANES_CASE(7) BWG_LANES_CASE(8)
+                default:
+                    break;
+            }
             continue;
         }
         const int v = ens[bi.ens].variant;

@@ -1,0 +1,127 @@
+"""The lanes engine's event loop where its windows, bytes and bounds end.
+
+Thresholds of every width the engine takes (1 to 32 planes: each number of
+Philox quads, whole and partial), windows of 32 events cut at every kind of
+place (ragged words, staggered replicas, launches of a few events, runs that
+cross a multiple of 2^32), states of weight zero, and totals that grow past
+the window's bound.  Exact against the oracle.
+"""
+
+import numpy as np
+import pytest
+
+import paper_2412_16613_amd as bwg
+from oracle import ssa
+from workloads import frank_network, paper_network
+from workloads.frank import (_A_TO_D, _A_TO_L, _AD_TO_2D, _AL_TO_2L, _LD_TO_2A, _net)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+def exact_network(n_tot, cu, ca, ci):
+    """Frank network with integer weights; 0 leaves the reactions out."""
+    rx = [(_A_TO_L, cu), (_A_TO_D, cu), (_AL_TO_2L, ca), (_AD_TO_2D, ca), (_LD_TO_2A, ci)]
+    rx = [r for r in rx if r[1]]
+    return _net([r[0] for r in rx], [r[1] for r in rx], n_tot, exact_integer=True)
+
+
+def check(torch, net, M, init, ops, seed=3, **kw):
+    print("case", net["n_tot"], net["rates"], M, init, ops, flush=True)
+    e = bwg.Ensemble(bwg.Network(net), M, seed=seed, net_id=5, engine="lanes", **kw)
+    o = ssa.OracleEnsemble(net, M, seed=seed, net_id=5)
+    e.init(init)
+    o.init(init)
+    for op, v in ops:
+        getattr(e, op)(v)
+        getattr(o, op)(v)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    ev, real = e.read_events()
+    np.testing.assert_array_equal(ev.cpu().numpy().astype(np.uint64), o.E)
+    want = np.zeros((M + 31) // 32, np.uint64)
+    np.add.at(want, np.arange(M) // 32, o.real.astype(np.uint64))
+    np.testing.assert_array_equal(real.cpu().numpy().astype(np.uint64), want)
+
+
+# n_tot of the paper's network by threshold planes 1 .. 20
+PAPER_N = {1: 2, 2: 3, 3: 4, 4: 6, 5: 8, 6: 11, 7: 16, 8: 20, 9: 32, 10: 40, 11: 60, 12: 90,
+           13: 120, 14: 180, 15: 250, 16: 360, 17: 500, 18: 700, 19: 1000, 20: 1400}
+
+
+@pytest.mark.parametrize("B", sorted(PAPER_N))
+def test_every_width_of_small_weights(torch, B):
+    net = paper_network(PAPER_N[B])
+    assert bwg.Network(net).quantized()["B"] == B
+    check(torch, net, 97, ("multinomial",), [("step", 333)])
+
+
+@pytest.mark.parametrize("B,n_tot,cu,ca,ci", [
+    (21, 1000, 100, 4, 4), (22, 1000, 900, 8, 8), (23, 1024, 164, 16, 16), (24, 3535, 177, 2, 2),
+    (25, 4000, 300, 4, 4), (26, 1000, 25000, 8, 8), (27, 1000, 20000, 256, 256),
+    (28, 1000, 70000, 512, 512), (29, 1000, 65535, 1024, 1024), (30, 1000, 65536, 2048, 2048),
+    (31, 1000, 131072, 4096, 4096), (32, 1000, 1 << 19, 8192, 8192),
+    (32, 12, 1 << 27, 1 << 24, 1 << 24)])
+def test_every_width_of_large_weights(torch, B, n_tot, cu, ca, ci):
+    net = exact_network(n_tot, cu, ca, ci)
+    assert bwg.Network(net).quantized()["B"] == B
+    check(torch, net, 65, ("fixed", (n_tot // 4, n_tot // 5, n_tot - n_tot // 4 - n_tot // 5)),
+          [("step", 500)])
+
+
+@pytest.mark.parametrize("cu,ca,ci", [(7, 0, 0), (0, 4, 0), (0, 0, 2), (5, 8, 0), (70000, 0, 64)])
+def test_absent_reactions(torch, cu, ca, ci):
+    net = exact_network(90, cu, ca, ci)
+    check(torch, net, 130, ("fixed", (30, 25, 35)), [("step", 700)])
+
+
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 64, 65, 255, 257])
+def test_ragged_words_and_staggered_replicas(torch, M):
+    check(torch, frank_network(50, k0=0.04), M, ("fixed", (0, 0, 50)),
+          [("advance", 1.0), ("step", 1), ("step", 31), ("advance", 3.0), ("step", 64)])
+
+
+@pytest.mark.parametrize("epl", [1, 31, 32, 33, 100])
+def test_launches_of_few_events(torch, epl):
+    check(torch, frank_network(64), 70, ("fixed", (0, 0, 64)), [("advance", 2.0), ("step", 90)],
+          events_per_launch=epl)
+
+
+def test_totals_that_outgrow_the_bound(torch):
+    # one L among A: the total climbs from almost nothing to its largest
+    # value within a few events, window after window
+    net = exact_network(200, 0, 64, 64)
+    check(torch, net, 333, ("fixed", (1, 0, 199)), [("step", 2000)])
+    # and a state that nothing leaves
+    check(torch, net, 40, ("fixed", (200, 0, 0)), [("step", 100)])
+
+
+@pytest.mark.parametrize("start", [(1 << 32) - 200, (1 << 34) - 31])
+def test_event_indices_cross_a_high_bit(torch, start):
+    net = frank_network(40, k0=0.05)
+    M = 77
+    e = bwg.Ensemble(bwg.Network(net), M, seed=8, net_id=1, engine="lanes")
+    o = ssa.OracleEnsemble(net, M, seed=8, net_id=1)
+    e.init_fixed((0, 0, 40))
+    o.init(("fixed", (0, 0, 40)))
+    e.advance(1.0)
+    o.advance(1.0)
+    # the same chain with every event index moved up (regions 3 and 4 of a
+    # checkpoint hold the events run and to reach)
+    blob = bytearray(e.save())
+    h = np.frombuffer(blob, dtype=np.uint64, count=32)
+    for k in range(int(h[11])):
+        if int(h[12 + 3 * k]) in (3, 4):
+            np.frombuffer(blob, dtype=np.uint64, count=int(h[14 + 3 * k]) // 8,
+                          offset=int(h[13 + 3 * k]))[:M] += np.uint64(start)
+    e.restore(bytes(blob))
+    o.E = o.E + np.uint64(start)
+    e.step(500)
+    o.step(500)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
