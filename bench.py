@@ -64,6 +64,16 @@ def word_event_slots(q, n_tot):
     return rng + select + masks + counts + products + unimolecular
 
 
+def lanes_event_slots(q, real_fraction):
+    """Slots per word-event of the lanes loop (one replica per lane, 64
+    word-events to a wave's window): the draws with the Philox calls' shared
+    rounds, the 8 x 8 bit transpositions of whole octets of planes, the test
+    of every replica's threshold byte (two instructions), and one application
+    (selection, count change, new weights) per real event."""
+    nq = (q["B"] + 3) // 4
+    return 5 + 32 * nq + 48 * ((nq + 1) // 2) + 64 + 33 * 32 * real_fraction
+
+
 # 32-bit VALU lane-operations/s: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz (a wave64
 # instruction in 4 cycles; the fp64 vector peak of 78.6 TFLOP/s is this lane rate of FMAs,
 # the fp32 157.3 counts packed pairs, which bitwise instructions do not have).  Measured by
@@ -214,9 +224,10 @@ def main():
     torch.cuda.set_device(dev)
     network = bwg.Network(net)
     q = network.quantized()
-    # counters were taken on the whole workload's bit-sliced launch
-    whole = args.shard == 1 and args.engine == "bitwise"
-    kernel = "wm_pc_kernel" if args.engine == "bitwise" else "wm_lanes_kernel"
+    # at these sizes both engines run the lanes loop; counters were taken on
+    # the whole workload's launch
+    whole = args.shard == 1
+    kernel = "wm_lanes_kernel"
 
     def make(engine):
         ens = bwg.Ensemble(network, M, seed=c["seed"], net_id=c["net_id"], engine=engine,
@@ -269,7 +280,7 @@ def main():
     value = events_per_step * args.steps / (r["ms"] / 1e3)
     adv_avg_ms = sum(r["adv_ms"]) / len(r["adv_ms"])
     word_events = events_per_step / 32.0
-    slots = word_event_slots(q, net["n_tot"])
+    slots = lanes_event_slots(q, r["real"] / events_per_step)
     # per event-kernel launch: its share of the step's word-events over its
     # duration (HIP events around each launch, on the launch stream)
     launches_per_step = r["kt_n"] / args.steps
@@ -299,21 +310,15 @@ def main():
         "replica_time_per_s": M * t_end * args.steps / (r["ms"] / 1e3),
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK / 1e12,
                      "unit": "T VALU lane-slots/s", "frac": achieved / VALU_PEAK,
-                     "traffic": measured_traffic("wm_pc_kernel") if whole else None,
+                     "traffic": measured_traffic(kernel) if whole else None,
                      "traffic_unit": "B/launch",
                      "kernel": kernel, "kernel_ms": launch_ms,
                      "launches_per_step": launches_per_step, "advance_ms": adv_avg_ms,
                      "slots_per_word_event": slots,
-                     "valu_insts_per_launch": measured_valu("wm_pc_kernel") if whole else None,
-                     "issued_frac": (measured_valu("wm_pc_kernel") * 64 / (launch_ms / 1e3) /
-                                     VALU_PEAK if whole and measured_valu("wm_pc_kernel")
-                                     else None)},
+                     "valu_insts_per_launch": measured_valu(kernel) if whole else None,
+                     "issued_frac": (measured_valu(kernel) * 64 / (launch_ms / 1e3) /
+                                     VALU_PEAK if whole and measured_valu(kernel) else None)},
     }
-    if args.engine == "lanes":
-        # the lane-slot count above is the bit-sliced word's algorithmic work;
-        # the one-replica-per-lane form has no such count of its own
-        out["roofline"].update(achieved=None, frac=None, slots_per_word_event=None,
-                               note="no algorithmic lane-slot count for the lanes engine")
     if not args.no_plain:
         p = run("plain", max(1, args.steps // 2), 1)
         pv = p["events"] * max(1, args.steps // 2) / (p["ms"] / 1e3)

@@ -635,6 +635,33 @@ static int check_engine(const bwg_net *n, int engine, const WmVariant **v,
     return fail(BWG_EINVAL, "unknown engine %d", engine);
 }
 
+// The lanes loop runs every Frank-family network within 32 threshold planes
+// and 32-bit total weights.
+static bool lanes_fit(const bwg_net *n)
+{
+    return n->shape_ok && n->q.B <= 32 && n->q.max_total < (1ll << 32) && pick_variant(n);
+}
+
+// Whether the next launch of a bit-sliced ensemble runs the lanes loop (the
+// same draws and results) instead of its word kernels.  A word's events are
+// one long chain, so up to one wave per SIMD (65536 words) a bit-sliced launch
+// takes the same time whatever its size, while the lanes loop's time falls
+// with the words.  Per 1000 events at 2^20 replicas (32768 words), words
+// against lanes: N_tot = 1024 1.09 against 0.65 to 0.89 ms (7 and 39 % of the
+// events real), N_tot = 32 0.70 against 0.52 ms (2 % real) or 1.15 ms (9 %);
+// at 2^19 replicas 1.09 against 0.36 to 0.49 and 0.70 against 0.29 or 0.66 ms.
+// The lines lie where the lanes loop still wins when most events are real: at
+// 49152 words from 10 count planes on (1.62 ms for one wave per word against
+// 0.97 to 1.32), at 24576 below.  An explicit block size or word width keeps
+// the word kernels, and shared thresholds (no draws per word) always do.
+static bool words_on_lanes(const bwg_ens *e)
+{
+    if (e->engine != BWG_ENGINE_BITWISE || e->lat || e->zs || e->block > 0 || e->keep_words ||
+        e->gvar || e->jit || !lanes_fit(e->net))
+        return false;
+    return (e->M + 31) / 32 <= (e->net->q.b >= 10 ? 49152u : 24576u);
+}
+
 extern "C" int bwg_ensemble_state_bytes(const bwg_net *n, uint64_t M, const bwg_opts *o,
                                         uint64_t *bytes)
 {
@@ -723,6 +750,7 @@ int bwg::ens_bind(bwg_ens *e, const bwg_net *n, uint64_t M, uint64_t seed, uint3
     e->timed = o && (o->flags & BWG_OPT_TIME_KERNELS);
     e->lat_stage = !(o && (o->flags & BWG_OPT_NO_LDS_STAGE));
     e->word_bits = (o && o->word_bits) ? (int)o->word_bits : 32;
+    e->keep_words = o && o->word_bits;
     e->zs = (o && (o->flags & BWG_OPT_SHARED_THRESHOLD)) ? (uint32_t)n->q.z_shared : 0;
     e->buf = (uint8_t *)dev_buf;
     e->bytes = buf_bytes;
@@ -771,7 +799,7 @@ extern "C" int bwg_ensemble_prepare(bwg_ens *e)
 {
     TraceRange trace_("bwg_ensemble_prepare");
     if (!e) return fail(BWG_EINVAL, "null ensemble");
-    if (e->lat || !e->want_jit_frank || e->jit_frank) return BWG_OK;
+    if (e->lat || !e->want_jit_frank || e->jit_frank || words_on_lanes(e)) return BWG_OK;
     return jit_frank_get(e->net, &e->jit_frank);
 }
 
@@ -954,8 +982,8 @@ static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s)
         a.zbase = e->zbase;
         a.zlen = e->zs ? e->zlen : 0;
         if (a.zs && !a.zlen) return fail(BWG_EINVAL, "shared thresholds not staged");
-        const bool frank_jit = e->engine == BWG_ENGINE_BITWISE && e->want_jit_frank &&
-                               e->block <= 0;
+        const bool lanes = e->engine == BWG_ENGINE_LANES || words_on_lanes(e);
+        const bool frank_jit = !lanes && e->want_jit_frank && e->block <= 0;
         if (frank_jit && !e->jit_frank) {
             const int jrc = jit_frank_get(e->net, &e->jit_frank);
             if (jrc) return jrc;
@@ -963,7 +991,7 @@ static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s)
         hipEvent_t ev = nullptr;
         int rc = mark_begin(e, s, &ev);
         if (rc) return rc;
-        if (e->engine == BWG_ENGINE_LANES)
+        if (lanes)
             HIP_TRY(launch_wm_lanes(a, s));
         else if (frank_jit)
             HIP_TRY(jit_launch(e->jit_frank, a, s));

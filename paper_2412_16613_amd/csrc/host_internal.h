@@ -99,6 +99,7 @@ struct bwg_ens {
     uint32_t net_id = 0;
     int engine = 0, block = 0;
     int word_bits = 32;   // replicas per thread of the bit-sliced engine
+    bool keep_words = false;  // a word width was asked for: always its kernels
     uint64_t table_cap = 0, epl = 0;
     uint8_t *buf = nullptr;
     uint64_t bytes = 0;

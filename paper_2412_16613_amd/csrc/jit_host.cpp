@@ -49,7 +49,7 @@ void jit_release(JitKernel *k)
     delete k;
 }
 
-// threads per block of the one-wave-per-word kernels: 128 below 65 536
+// threads per block of the one-wave-per-word kernels: 128 up to 32 768
 // words, 256 from there (measured 1.3-1.5x on general networks at 2^21 and
 // 2^22 replicas; 128-thread blocks are placed unevenly there), as for the
 // precompiled Frank kernels
@@ -521,7 +521,7 @@ hipError_t jit_launch(const JitKernel *k, const WmArgs &a, hipStream_t s)
         // shared thresholds (Frank kernels only): one wave per word, the
         // block sizes of the precompiled shared-threshold kernels
         if (!k->sh) return hipErrorInvalidValue;
-        const unsigned block = a.n_words >= 65536 ? 256u : 128u;
+        const unsigned block = a.n_words > 32768 ? 256u : 128u;
         const unsigned grid = (unsigned)((a.n_words + block - 1) / block);
         return hipModuleLaunchKernel(k->sh, grid, 1, 1, block, 1, 1, 0, s, params, nullptr);
     }
@@ -532,7 +532,7 @@ hipError_t jit_launch(const JitKernel *k, const WmArgs &a, hipStream_t s)
         return hipModuleLaunchKernel(k->pc, grid, 1, 1, 256, 1, 1, 0, s, params, nullptr);
     }
     const unsigned block =
-        (unsigned)(a.n_words >= 65536 ? kJitBlockLarge : kJitBlockSmall);
+        (unsigned)(a.n_words > 32768 ? kJitBlockLarge : kJitBlockSmall);
     const unsigned grid = (unsigned)((a.n_words + block - 1) / block);
     return hipModuleLaunchKernel(k->fn, grid, 1, 1, block, 1, 1, 0, s, params, nullptr);
 }

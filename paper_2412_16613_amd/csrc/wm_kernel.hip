@@ -97,10 +97,11 @@ hipError_t launch_wm(const WmArgs &a, hipStream_t s, int block, int word_bits)
         return hipGetLastError();
     }
     // 128-thread blocks leave two SIMDs of a CU to other blocks, which pays
-    // while there are fewer words than one wave per SIMD; from 1024 waves on,
-    // 256-thread blocks (one wave per SIMD of a CU) keep the waves spread
-    // evenly when the occupancy would let some CUs take more than their share
-    if (block <= 0) block = a.n_words >= 65536 ? 256 : 128;
+    // while there are few words; past half a wave of 64 words per SIMD they
+    // are placed two to a SIMD with others idle (2^20 x 1.5 replicas, 3000
+    // events of the N_tot = 1024 network: 7.19 ms, against 4.86 ms for 2^21
+    // replicas in 256-thread blocks, one wave on each SIMD of a CU)
+    if (block <= 0) block = a.n_words > 32768 ? 256 : 128;
     const uint64_t grid = (a.n_words + block - 1) / block;
     if (a.zs)
         hipLaunchKernelGGL((wm_event_kernel<NB, BC, FA, CU, true, NT, BS>), dim3((uint32_t)grid),

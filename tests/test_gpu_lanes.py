@@ -125,3 +125,45 @@ def test_event_indices_cross_a_high_bit(torch, start):
     o.step(500)
     np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
     np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
+
+
+# ---- which loop a bit-sliced ensemble runs --------------------------------------
+
+@pytest.mark.parametrize("net,init", [
+    (frank_network(32), ("fixed", (0, 0, 32))),                 # precompiled weights
+    (frank_network(1024), ("fixed", (0, 0, 1024))),
+    (frank_network(100, k0=0.03), ("fixed", (0, 0, 100))),      # compiled for the network
+    (paper_network(64), ("multinomial",)),
+], ids=["frank32", "frank1024", "frank100", "paper64"])
+def test_word_kernels_of_small_ensembles(torch, net, init):
+    """A word width asked for keeps the word kernels, which small ensembles
+    no longer run by default."""
+    M = 4096 + 77
+    e = bwg.Ensemble(bwg.Network(net), M, seed=6, net_id=2, word_bits=32)
+    o = ssa.OracleEnsemble(net, M, seed=6, net_id=2)
+    e.init(init)
+    o.init(init)
+    for t in (0.2, 0.9):
+        e.advance(t)
+        o.advance(t)
+    e.step(60)
+    o.step(60)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
+
+
+@pytest.mark.parametrize("n_tot,words", [(32, 24576), (1024, 49152)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_both_sides_of_the_size_rule(torch, n_tot, words, more):
+    """Around the size at which the default leaves the lanes loop, every
+    choice gives the same state."""
+    M = 32 * words + more
+    net = bwg.Network(frank_network(n_tot))
+    got = []
+    for kw in (dict(), dict(word_bits=32), dict(engine="lanes")):
+        e = bwg.Ensemble(net, M, seed=2, **kw)
+        e.init_fixed((0, 0, n_tot)).advance(0.2).step(40)
+        got.append((e.read_counts(), *e.read_events()))
+    for g in got[1:]:
+        for x, y in zip(g, got[0]):
+            assert bool((x == y).all())
