@@ -136,6 +136,40 @@ __global__ __launch_bounds__(64, 2) void wm_persistent_kernel(const BatchEns *en
     }
 }
 
+// The queue of a batch whose members all run the lanes loop: n2 two-word
+// items, then n64 items of 64 words whose 32 pairs of words are taken one at
+// a time, so that a member's words spread over the chip (a pair is a wave's
+// work).  Without the word functions' 256 registers, four waves fit a SIMD
+// where wm_persistent_kernel has two.
+__global__ __launch_bounds__(64, 4) void wm_persistent_lanes_kernel(const BatchEns *ens,
+                                                                    const BatchItem *items,
+                                                                    uint32_t n2, uint32_t n64,
+                                                                    uint32_t *counter,
+                                                                    uint64_t max_events)
+{
+    extern __shared__ __align__(16) uint32_t sq_dyn[];
+    const int half = threadIdx.x >> 5;
+    for (;;) {
+        uint32_t it = 0;
+        if (threadIdx.x == 0) it = atomicAdd(counter, 1u);
+        it = uni32(__shfl(it, 0));
+        if (it >= n2 + 32 * n64) break;
+        const bool pair = it >= n2;
+        const uint32_t p = pair ? it - n2 : 0;
+        const BatchItem bi = items[pair ? n2 + p / 32 : it];
+        const uint32_t k = uni32(bi.ens) & ~BATCH_ITEM_LANES;
+        const uint64_t w0 = (uint64_t)uni32(bi.word0) + 2 * (p % 32);
+        if (w0 >= uni64(ens[k].a.n_words)) continue;
+        const uint64_t w = w0 + half;
+        switch ((uni32((uint32_t)ens[k].a.B) + 3) / 4) {
+            BWG_LANES_CASE(1) BWG_LANES_CASE(2) BWG_LANES_CASE(3) BWG_LANES_CASE(4)
+            BWG_LANES_CASE(5) BWG_LANES_CASE(6) BWG_LANES_CASE(7) BWG_LANES_CASE(8)
+            default:
+                break;
+        }
+    }
+}
+
 // Budgets of every ensemble of a batch in one launch: thread g belongs to
 // the ensemble whose replica range [offset, offset + M) holds it.
 __global__ void batch_budget_kernel(const BatchBudget *bb, int n_ens, uint64_t total, uint64_t g0)
@@ -193,6 +227,16 @@ hipError_t launch_persistent(const BatchEns *ens, const BatchItem *items, uint32
     const size_t lds = lanes ? 2 * kLanesHalfWords * sizeof(uint32_t) : 0;
     hipLaunchKernelGGL(wm_persistent_kernel, dim3((uint32_t)waves), dim3(64), lds, s, ens, items,
                        n_items, counter, max_events);
+    return hipGetLastError();
+}
+
+hipError_t launch_persistent_lanes(const BatchEns *ens, const BatchItem *items, uint32_t n2,
+                                   uint32_t n64, uint32_t *counter, int waves,
+                                   uint64_t max_events, hipStream_t s)
+{
+    const size_t lds = 2 * kLanesHalfWords * sizeof(uint32_t);
+    hipLaunchKernelGGL(wm_persistent_lanes_kernel, dim3((uint32_t)waves), dim3(64), lds, s, ens,
+                       items, n2, n64, counter, max_events);
     return hipGetLastError();
 }
 

@@ -26,6 +26,8 @@ struct bwg_batch {
     uint64_t cap_items = 0;
     uint64_t n_items = 0;          // items of the current members
     bool lanes_items = false;      // the staged queue holds lanes items
+    bool all_lanes = false;        // every word of every member runs the lanes loop
+    uint64_t n_pairs = 0;          // two-word items at the head of such a queue
     // device layout (caller buffer)
     BatchEns *d_ens = nullptr;
     BatchBudget *d_budget = nullptr;
@@ -82,6 +84,25 @@ static uint64_t n_items_of(const bwg_ens *e)
 {
     const uint64_t words = (e->M + 31) / 32, split = std::min(lanes_split(e), words);
     return (split + 63) / 64 + (words - split + 1) / 2;
+}
+
+// Whether every word of the batch runs the lanes loop.  The word functions of
+// the persistent kernel take shifts and weights at run time (1.8 times the
+// compiled kernels' instructions) and hold a whole chain in one lane: 24
+// uneven networks take 180 ms on them and 17 on the lanes loop, the 256 of the
+// uneven batch 1.5 s (0.43 with the long chains picked for lanes items) and
+// 0.22, 40 small networks of 200000 replicas 5.1 and 5.0 ms.  Only members
+// that were given a word width, or that fill the chip with words by
+// themselves (65536 of them), keep the batch on the word functions.
+static bool batch_on_lanes(bwg_ens *const *ens, size_t n)
+{
+    uint64_t pairs = 0;
+    for (size_t k = 0; k < n; ++k) {
+        const uint64_t words = (ens[k]->M + 31) / 32;
+        if (ens[k]->keep_words || words > 65536) return false;
+        pairs += (words + 63) / 64 * 32;
+    }
+    return pairs < (1ull << 31);
 }
 
 static uint64_t layout_bytes(int n, uint64_t items, uint64_t *off_ens, uint64_t *off_budget,
@@ -268,21 +289,30 @@ static int stage_items(bwg_batch *b, hipStream_t s)
     std::vector<std::pair<double, BatchItem>> q;
     q.reserve(b->n_items);
     b->lanes_items = false;
+    b->all_lanes = batch_on_lanes(b->ens.data(), b->ens.size());
+    b->n_pairs = 0;
     for (size_t k = 0; k < b->ens.size(); ++k) {
         const bwg_ens *e = b->ens[k];
         const uint64_t words = (e->M + 31) / 32, split = std::min(lanes_split(e), words);
-        const double cw = b->cost[k] * (double)e->pending;
+        const double cw = (b->all_lanes ? b->lane_cost[k] : b->cost[k]) * (double)e->pending;
         const double cl = b->lane_cost[k] * (double)e->pending;
         for (uint64_t w0 = 0; w0 < split; w0 += 64)
             q.push_back({cw, BatchItem{(uint32_t)k, (uint32_t)w0}});
         for (uint64_t w0 = split; w0 < words; w0 += 2)
             q.push_back({cl, BatchItem{(uint32_t)k | BATCH_ITEM_LANES, (uint32_t)w0}});
-        if (split < words) b->lanes_items = true;
+        if (split < words) {
+            b->lanes_items = true;
+            b->n_pairs += (words - split + 1) / 2;
+        }
     }
+    using Item = std::pair<double, BatchItem>;
     if (b->order == 0)
         std::stable_sort(q.begin(), q.end(),
-                         [](const std::pair<double, BatchItem> &x,
-                            const std::pair<double, BatchItem> &y) { return x.first > y.first; });
+                         [](const Item &x, const Item &y) { return x.first > y.first; });
+    if (b->all_lanes)  // two-word items (asked for: the longest chains) first
+        std::stable_partition(q.begin(), q.end(), [](const Item &x) {
+            return (x.second.ens & BATCH_ITEM_LANES) != 0;
+        });
     for (size_t i = 0; i < q.size(); ++i) b->h_items[i] = q[i].second;
     if (!q.empty())
         HIP_TRY(hipMemcpyAsync(b->d_items, b->h_items, sizeof(BatchItem) * q.size(),
@@ -397,6 +427,13 @@ static int enqueue_pass(bwg_batch *b, uint64_t max_events, hipStream_t s)
 {
     if (!b->n_items) return BWG_OK;
     HIP_TRY(launch_batch_prologue(b->d_counter, s));
+    if (b->all_lanes) {
+        // four of its waves fit a SIMD where two of the word kernel's do
+        HIP_TRY(launch_persistent_lanes(b->d_ens, b->d_items, (uint32_t)b->n_pairs,
+                                        (uint32_t)(b->n_items - b->n_pairs), b->d_counter,
+                                        b->waves * 2, max_events, s));
+        return BWG_OK;
+    }
     HIP_TRY(launch_persistent(b->d_ens, b->d_items, (uint32_t)b->n_items, b->d_counter, b->waves,
                               max_events, b->lanes_items, s));
     return BWG_OK;

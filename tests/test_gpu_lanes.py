@@ -167,3 +167,32 @@ def test_both_sides_of_the_size_rule(torch, n_tot, words, more):
     for g in got[1:]:
         for x, y in zip(g, got[0]):
             assert bool((x == y).all())
+
+
+@pytest.mark.parametrize("word_bits", [0, 32], ids=["lanes", "words"])
+def test_batch_queues(torch, word_bits):
+    """The two persistent kernels: a batch on the lanes loop (64-word items
+    taken by pairs of words, and two-word items asked for), and one that a
+    given word width keeps on the word functions beside lanes items."""
+    mix = [(frank_network(16, k0=0.05), 33, 12.0), (frank_network(100, k0=0.01), 4200, 3.0),
+           (frank_network(40, k0=0.1), 2048, 6.0), (frank_network(1000, k0=0.02), 97, 0.75),
+           (exact_network(90, 7, 0, 0), 65, 0.05)]
+    ens, alone = [], []
+    for k, (net, M, _) in enumerate(mix):
+        for out, kw in ((ens, dict(word_bits=word_bits)), (alone, dict(engine="lanes"))):
+            e = bwg.Ensemble(bwg.Network(net), M, seed=3, net_id=k, **kw)
+            out.append(e.init_fixed((0, 0, net["n_tot"])))
+    ens[0].set_engine("lanes")
+    ens[1].set_lanes_words(70)
+    b = bwg.Batch(ens, waves=100)
+    t = [m[2] for m in mix]
+    b.advance(t)
+    for e, x in zip(ens, t):
+        e.schedule(2 * x)
+    while any(e.pending() for e in ens):
+        b.run(250)
+    for e, f, x in zip(ens, alone, t):
+        f.advance(x).advance(2 * x)
+        np.testing.assert_array_equal(e.read_counts().cpu().numpy(), f.read_counts().cpu().numpy())
+        for u, v in zip(e.read_events(), f.read_events()):
+            np.testing.assert_array_equal(u.cpu().numpy(), v.cpu().numpy())
