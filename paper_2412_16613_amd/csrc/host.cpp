@@ -662,6 +662,24 @@ static bool words_on_lanes(const bwg_ens *e)
     return (e->M + 31) / 32 <= (e->net->q.b >= 10 ? 49152u : 24576u);
 }
 
+// Whether a general ensemble of this many words runs the lanes kernel compiled
+// for the network or its word kernels.  A word's event costs a shifted
+// subtraction per set bit of every weight (two instructions a plane) and
+// updates every replica, the lanes loop's a multiply-add per reaction for the
+// replicas with a real event.  Per 200 events, words against lanes: 12
+// reactions with 67 set bits 1.47 against 0.16 ms at 2^19 replicas, 2.45
+// against 1.13 at 2^22; 5 reactions with 24 set bits 0.60 / 0.14 and 1.08 /
+// 0.97 ms; 3 reactions with 5 set bits 0.22 / 0.08 and 0.53 / 0.50 ms; one
+// reaction with one set bit (81 % of the events real) 0.13 / 0.09 at 2^19 and
+// 0.14 / 0.16 at 2^20.
+static bool general_on_lanes(const bwg_net *n, uint64_t words)
+{
+    if (!jit_lanes_fits(n)) return false;
+    int bits = 0;
+    for (int j = 0; j < n->R; ++j) bits += __builtin_popcountll((uint64_t)n->q.c[j]);
+    return words <= (bits >= 32 ? ~0ull : (bits >= 4 ? 65536u : 24576u));
+}
+
 extern "C" int bwg_ensemble_state_bytes(const bwg_net *n, uint64_t M, const bwg_opts *o,
                                         uint64_t *bytes)
 {
@@ -763,7 +781,10 @@ int bwg::ens_bind(bwg_ens *e, const bwg_net *n, uint64_t M, uint64_t seed, uint3
     bool want_gen = false;
     jit_plan(n, e->engine, e->var, generic, jit_ok, &want_gen, &e->want_jit_frank);
     if (want_gen) {
-        const int rc = jit_get(const_cast<bwg_net *>(n), &e->jit);
+        bwg_net *nm = const_cast<bwg_net *>(n);
+        const int rc = general_on_lanes(n, (M + 31) / 32) && !e->keep_words
+                           ? jit_lanes_get(nm, &e->jit)
+                           : jit_get(nm, &e->jit);
         if (rc) return rc;
     }
     const Layout L = layout(n, M, e->engine, e->table_cap, e->var);

@@ -83,13 +83,15 @@ struct bwg_net {
     std::map<uint64_t, Table> tables;  // keyed by the bits of mu
     bwg::JitKernel *jit = nullptr;     // compiled on the first ensemble that needs it
     bwg::JitKernel *jit_frank = nullptr;  // compiled Frank-family kernel (run-time weights)
-    std::vector<char> jit_code, jit_frank_code;  // their code objects (gfx950)
+    bwg::JitKernel *jit_lanes = nullptr;  // compiled lanes kernel (general path)
+    std::vector<char> jit_code, jit_frank_code, jit_lanes_code;  // their code objects (gfx950)
     ~bwg_net()
     {
         for (auto &kv : tables)
             if (kv.second.host) (void)hipHostFree(kv.second.host);
         bwg::jit_release(jit);
         bwg::jit_release(jit_frank);
+        bwg::jit_release(jit_lanes);
     }
 };
 
@@ -108,6 +110,7 @@ struct bwg_ens {
     const bwg::WmVariant *var = nullptr;
     const bwg::GenVariant *gvar = nullptr;  // general kernel (non-Frank or forced)
     const bwg::JitKernel *jit = nullptr;    // its per-network compiled form, if used
+                                            // (word kernels, or the lanes kernel)
     const bwg::JitKernel *jit_frank = nullptr;  // compiled Frank kernel for a run-time variant
     bool want_jit_frank = false;                // build it at the first bit-sliced launch
     uint32_t *planes = nullptr;
@@ -160,6 +163,10 @@ int ens_bind(bwg_ens *e, const bwg_net *n, uint64_t M, uint64_t seed, uint32_t n
 int get_table(bwg_net *n, double mu, const Table **out, bool pinned = true);
 // The network's run-time compiled kernel (compiled on the first call).
 int jit_get(bwg_net *n, const JitKernel **out);
+// The network's compiled lanes kernel on the general path (compiled on the
+// first call), and whether it has one.
+int jit_lanes_get(bwg_net *n, const JitKernel **out);
+bool jit_lanes_fits(const bwg_net *n);
 // The network's compiled Frank-family kernel (compiled on the first call),
 // and whether the network fits that kernel's template parameters.
 int jit_frank_get(bwg_net *n, const JitKernel **out);

@@ -22,6 +22,7 @@
 
 #include <hip/hiprtc.h>
 
+#include <algorithm>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -39,6 +40,7 @@ struct JitKernel {
     hipFunction_t fn = nullptr;  // one thread per word
     hipFunction_t pc = nullptr;  // producer/consumer form
     hipFunction_t sh = nullptr;  // Frank kernels: one shared threshold per event
+    hipFunction_t lanes = nullptr;  // one replica per thread (alone in its module)
     bool frank = false;          // the Frank-family kernel of wm_device.h
 };
 
@@ -325,6 +327,151 @@ static std::string jit_source_wide(const bwg_net &n, int NB, int BC)
     return o.str();
 }
 
+// Source of network n's lanes kernel (lanes_device.h: one replica per thread,
+// null events skipped): the replica's counts packed two to a register (16 bits
+// each; a closed network's last species is what the conserved total leaves),
+// the cumulative weights of its state in 32-bit arithmetic, and first crossing
+// as one select per reaction from the last to the first.  Same draws and
+// results as the kernels above.
+static std::string jit_source_lanes(const bwg_net &n)
+{
+    const int S = n.S;
+    auto dv = [&](int j, int x) { return n.prod[j * S + x] - n.reac[j * S + x]; };
+    auto changes = [&](int j) {
+        for (int x = 0; x < S; ++x)
+            if (dv(j, x)) return true;
+        return false;
+    };
+    int R = n.R;  // reactions up to the last one that changes the state
+    while (R > 0 && !changes(R - 1)) --R;
+    std::vector<int> rx;
+    for (int j = 0; j < R; ++j)
+        if (n.q.c[j]) rx.push_back(j);
+    const int kept = n.open ? S : S - 1;  // species held; the last follows if closed
+    const int regs = (kept + 1) / 2;
+    const uint64_t nt = (uint64_t)n.n_tot;
+    std::ostringstream o;
+    o << "#include \"lanes_device.h\"\n"
+      << "namespace bwg {\n"
+      << "struct NetReplica {\n"
+      << "    static constexpr int S = " << S << ";\n"
+      << "    uint32_t nt, n[S], p[" << std::max(regs, 1) << "], s[" << rx.size() + 1 << "];\n"
+      << "    __device__ __forceinline__ explicit NetReplica(const WmArgs &) {}\n"
+      << "    __device__ __forceinline__ void set_counts(const uint32_t (&N)[S])\n    {\n"
+      << "        nt = 0;\n        p[0] = 0;\n"
+      << "        for (int x = 0; x < S; ++x) nt += N[x];\n";
+    for (int k = 0; k < regs; ++k) {
+        o << "        p[" << k << "] = N[" << 2 * k << "]";
+        if (2 * k + 1 < kept) o << " | N[" << 2 * k + 1 << "] << 16";
+        o << ";\n";
+    }
+    o << "        weigh();\n    }\n"
+      << "    __device__ __forceinline__ void get_counts(uint32_t (&N)[S]) const\n    {\n"
+      << "        for (int x = 0; x < S; ++x) N[x] = n[x];\n    }\n"
+      << "    __device__ __forceinline__ void weigh()\n    {\n";
+    for (int x = 0; x < kept; ++x)
+        o << "        n[" << x << "] = p[" << x / 2 << "]" << (x % 2 ? " >> 16" : " & 0xFFFFu")
+          << ";\n";
+    if (kept < S) {
+        o << "        n[" << S - 1 << "] = (nt";
+        for (int x = 0; x < kept; ++x) o << " - n[" << x << "]";
+        o << ") & 0xFFFFu;\n";
+    }
+    // weight factors, each formed once, and the cumulative weights
+    std::vector<std::string> made;
+    for (size_t i = 0; i < rx.size(); ++i) {
+        const int j = rx[i];
+        int xs[2], k = 0;
+        for (int x = 0; x < S; ++x)
+            for (int m = 0; m < n.reac[j * S + x]; ++m) xs[k++] = x;
+        std::string h;
+        uint64_t most = nt;
+        const std::string a = "n[" + std::to_string(xs[0]) + "]";
+        if (k == 1) {
+            h = a;
+        } else {
+            h = "h" + std::to_string(xs[0]) + std::to_string(xs[1]);
+            if (std::find(made.begin(), made.end(), h) == made.end()) {
+                made.push_back(h);
+                if (xs[0] != xs[1])
+                    o << "        const uint32_t " << h << " = " << a << " * n[" << xs[1] << "];\n";
+                else
+                    o << "        const uint32_t " << h << " = (" << a << " * ((" << a
+                      << " - 1u) & 0xFFFFu)) >> 1;\n";
+            }
+            most = nt * nt;
+        }
+        const uint64_t c = (uint64_t)n.q.c[j];
+        o << "        s[" << i << "] = ";
+        if (i) o << "s[" << i - 1 << "] + ";
+        if (c == 1)
+            o << h;
+        else if (c < (1u << 24) && most < (1u << 24))
+            o << "mul24(" << h << ", " << c << "u)";
+        else
+            o << c << "u * " << h;
+        o << ";\n";
+    }
+    if (rx.empty()) o << "        s[0] = 0;\n";
+    // the slack of the bound: a quarter of the total and about two events'
+    // change of the largest weight
+    uint64_t step = 0;
+    for (int j : rx) {
+        int order = 0;
+        for (int x = 0; x < S; ++x) order += n.reac[j * S + x];
+        step = std::max(step, 2 * (uint64_t)n.q.c[j] * (order == 2 ? nt : 1));
+    }
+    step = std::min<uint64_t>(step, 1u << 28);
+    o << "    }\n"
+      << "    __device__ __forceinline__ uint32_t total() const { return s["
+      << (rx.empty() ? 0 : rx.size() - 1) << "]; }\n"
+      << "    __device__ __forceinline__ uint32_t bound() const\n    {\n"
+      << "        const uint32_t t = total();\n"
+      << "        return t ? __builtin_elementwise_add_sat(t, (t >> 2) + " << step << "u) : 0u;\n"
+      << "    }\n"
+      << "    __device__ __forceinline__ uint64_t fire(uint32_t t, bool on, uint64_t)\n    {\n"
+      << "        t = on ? t : ~0u;\n";
+    for (int k = 0; k < regs; ++k) o << "        uint32_t d" << k << " = 0;\n";
+    for (size_t i = rx.size(); i-- > 0;) {
+        const int j = rx[i];
+        o << "        {\n            const bool lt = t < s[" << i << "];\n";
+        std::string blocked;
+        if (n.open)
+            for (int x = 0; x < S; ++x)
+                if (dv(j, x) > 0)
+                    blocked += (blocked.empty() ? "" : " || ") + ("n[" + std::to_string(x) + "] > ") +
+                               std::to_string(n.n_tot - dv(j, x)) + "u";
+        if (!blocked.empty()) o << "            const bool blocked = " << blocked << ";\n";
+        for (int k = 0; k < regs; ++k) {
+            int32_t d = dv(j, 2 * k);
+            if (2 * k + 1 < kept) d += dv(j, 2 * k + 1) * 65536;
+            o << "            d" << k << " = lt ? ";
+            if (blocked.empty() || !d)
+                o << (uint32_t)d << "u";
+            else
+                o << "(blocked ? 0u : " << (uint32_t)d << "u)";
+            o << " : d" << k << ";\n";
+        }
+        o << "        }\n";
+    }
+    o << "        uint64_t changed = 0;\n";
+    for (int k = 0; k < regs; ++k)
+        o << "        changed |= ballot(d" << k << " != 0);\n"
+          << "        p[" << k << "] += d" << k << ";\n";
+    o << "        weigh();\n"
+      << "        return changed;\n    }\n"
+      << "};\n"
+      << "constexpr int NQ = " << (n.q.B + 3) / 4 << ";\n"
+      << "extern \"C\" __global__ __launch_bounds__(256) void bwg_jit_lanes(WmArgs a, uint64_t w0)\n"
+      << "{\n"
+      << "    __shared__ __align__(16) uint32_t sq[8][LanesRow<NQ>::HALF];\n"
+      << "    const int half = threadIdx.x >> 5;\n"
+      << "    wm_lanes<NQ, NetReplica>(a, w0 + 8 * (uint64_t)blockIdx.x + half, sq[half]);\n"
+      << "}\n"
+      << "}  // namespace bwg\n";
+    return o.str();
+}
+
 // Compiles src with hipRTC for gfx950 into a code object: host work only,
 // no device needed.
 static int jit_build(const std::string &src, std::vector<char> *code)
@@ -370,6 +517,48 @@ static int jit_load(const std::vector<char> &code, bool frank, JitKernel **out)
         return fail(BWG_EDEVICE, "loading the network's kernel: %s", hipGetErrorString(e));
     }
     *out = k;
+    return BWG_OK;
+}
+
+// The lanes kernel of a network that has one (jit_lanes_fits).
+static int jit_load_lanes(const std::vector<char> &code, JitKernel **out)
+{
+    auto k = new JitKernel();
+    hipError_t e = hipModuleLoadData(&k->mod, code.data());
+    if (e == hipSuccess) e = hipModuleGetFunction(&k->lanes, k->mod, "bwg_jit_lanes");
+    if (e != hipSuccess) {
+        jit_release(k);
+        return fail(BWG_EDEVICE, "loading the network's kernel: %s", hipGetErrorString(e));
+    }
+    *out = k;
+    return BWG_OK;
+}
+
+// 32-bit thresholds and totals, on the general path.
+bool jit_lanes_fits(const bwg_net *n)
+{
+    return (n->gen_ok || n->wide_ok) && n->q.B <= 32 && n->q.max_total < (1ll << 32) &&
+           n->q.b <= 14;
+}
+
+static int jit_lanes_code(bwg_net *n)
+{
+    if (!n->jit_lanes_code.empty()) return BWG_OK;
+    return jit_build(jit_source_lanes(*n), &n->jit_lanes_code);
+}
+
+int jit_lanes_get(bwg_net *n, const JitKernel **out)
+{
+    std::lock_guard<std::mutex> lock(n->mu);
+    if (!n->jit_lanes) {
+        int rc = jit_lanes_code(n);
+        if (rc) return rc;
+        JitKernel *k = nullptr;
+        rc = jit_load_lanes(n->jit_lanes_code, &k);
+        if (rc) return rc;
+        n->jit_lanes = k;
+    }
+    *out = n->jit_lanes;
     return BWG_OK;
 }
 
@@ -509,6 +698,7 @@ int jit_build_codes(bwg_net *n, bool general, bool frank)
 {
     std::lock_guard<std::mutex> lock(n->mu);
     int rc = general ? jit_general_code(n) : BWG_OK;
+    if (!rc && general && jit_lanes_fits(n)) rc = jit_lanes_code(n);
     if (!rc && frank) rc = jit_frank_code(n);
     return rc;
 }
@@ -516,6 +706,17 @@ int jit_build_codes(bwg_net *n, bool general, bool frank)
 hipError_t jit_launch(const JitKernel *k, const WmArgs &a, hipStream_t s)
 {
     WmArgs arg = a;
+    if (k->lanes) {
+        // 8 words to a 256-thread block, one work-item per replica slot
+        hipError_t err = hipSuccess;
+        const hipError_t last = launch_pieces(32 * a.n_words, 256, [&](uint64_t i0, dim3 g) {
+            uint64_t w0 = i0 / 32;
+            void *params[] = {&arg, &w0};
+            if (err == hipSuccess)
+                err = hipModuleLaunchKernel(k->lanes, g.x, 1, 1, 256, 1, 1, 0, s, params, nullptr);
+        });
+        return err != hipSuccess ? err : last;
+    }
     void *params[] = {&arg};
     if (a.zs) {
         // shared thresholds (Frank kernels only): one wave per word, the

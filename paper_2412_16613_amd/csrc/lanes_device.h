@@ -140,6 +140,15 @@ struct EventDraw {
     }
 };
 
+__device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+__device__ __forceinline__ bool wave_any(bool v) { return ballot(v) != 0; }
+
+// Low 32 bits of a product of numbers below 2^24, at full rate.
+__device__ __forceinline__ uint32_t mul24(uint32_t x, uint32_t y)
+{
+    return (x & 0xFFFFFFu) * (y & 0xFFFFFFu);
+}
+
 // A Frank-family replica: the counts of L and D in one register (A is what
 // the conserved total leaves) and the cumulative weights of its state,
 // S_1 = U, S_2 = 2U, S_3 = 2U + 2^fa A L, S_4 = 2U + 2^fa A (L + D),
@@ -200,19 +209,18 @@ struct FrankReplica {
     }
     // The reaction whose cumulative weight first exceeds n (A -> L, A -> D,
     // A + L -> 2L, A + D -> 2D, L + D -> 2A) if on and n < s5, without
-    // branches.
-    __device__ __forceinline__ void fire(uint32_t n, bool on)
+    // branches; returns the lanes whose state changed (onm: the lanes of on).
+    __device__ __forceinline__ uint64_t fire(uint32_t n, bool on, uint64_t onm)
     {
+        const uint64_t fired = ballot(n < s5) & onm;
         const bool isL = n < s1 || (n >= s2 && n < s3);
         const bool isI = n >= s4;
         const uint32_t d = isI ? 0xFFFEFFFFu : (isL ? 1u : 0x10000u);
         ld += on && n < s5 ? d : 0u;
         weigh();
+        return fired;
     }
 };
-
-__device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
-__device__ __forceinline__ bool wave_any(bool v) { return ballot(v) != 0; }
 
 // Low k bits set, k in 0 .. 32.
 __device__ __forceinline__ uint32_t low_bits(uint32_t k)
@@ -411,8 +419,7 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
                     const uint32_t left = cm & (cm - 1);
                     cm = on ? left : cm;
                     const uint32_t nn = threshold(__builtin_ctz(cm | 0x80000000u));
-                    const uint64_t fired = ballot(n < rep.total()) & onm;
-                    rep.fire(n, on);
+                    const uint64_t fired = rep.fire(n, on, onm);
                     real0 += (uint32_t)__builtin_popcount((uint32_t)fired);
                     real1 += (uint32_t)__builtin_popcount((uint32_t)(fired >> 32));
                     on = cm != 0 && rep.total() <= bound;
@@ -454,7 +461,7 @@ __device__ __forceinline__ void wm_lanes_shared(const WmArgs &a, uint64_t w)
         const uint32_t n = shared_at(a, e);
         const bool on = v.mine && v.E0 <= e && e < v.T0;
         nreal += on && n < rep.total() ? 1u : 0u;
-        rep.fire(n, on);
+        rep.fire(n, on, 0);
     }
     for (int o = 16; o; o >>= 1) nreal += (uint32_t)__shfl_xor((int)nreal, o, 32);
     rep.get_counts(N);

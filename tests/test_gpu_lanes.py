@@ -12,7 +12,8 @@ import pytest
 
 import paper_2412_16613_amd as bwg
 from oracle import ssa
-from workloads import frank_network, paper_network
+from workloads import (frank_network, open_network, paper_network, random_network,
+                       random_wide_network)
 from workloads.frank import (_A_TO_D, _A_TO_L, _AD_TO_2D, _AL_TO_2L, _LD_TO_2A, _net)
 
 pytestmark = pytest.mark.gpu
@@ -196,3 +197,59 @@ def test_batch_queues(torch, word_bits):
         np.testing.assert_array_equal(e.read_counts().cpu().numpy(), f.read_counts().cpu().numpy())
         for u, v in zip(e.read_events(), f.read_events()):
             np.testing.assert_array_equal(u.cpu().numpy(), v.cpu().numpy())
+
+
+# ---- networks on the general path ------------------------------------------------
+
+def table(species, reactions, rates, n_tot, open_net=False):
+    net = _net(reactions, rates, n_tot, exact_integer=True)
+    net["species"] = tuple("S%d" % x for x in range(species))
+    net["hop_rates"] = [0.0] * species
+    net["open"] = open_net
+    return net
+
+
+GENERAL = {
+    "random12": (random_network(2, 200, 12), ("multinomial",)),
+    "random16": (random_network(3, 12, 16), ("multinomial",)),
+    # weights and products beyond 24 bits
+    "heavy": (table(3, [((2, 0, 0), (0, 1, 1)), ((0, 1, 1), (2, 0, 0)), ((0, 0, 1), (0, 1, 0))],
+                    [1 << 25, 3 << 23, (1 << 26) + 5], 8), ("fixed", (3, 3, 2))),
+    "crowd": (table(3, [((1, 1, 0), (0, 1, 1)), ((0, 2, 0), (1, 1, 0)), ((0, 0, 1), (1, 0, 0))],
+                    [3, 2, 70000], 9000), ("fixed", (3000, 2500, 3500))),
+    # a ghost between reactions that change the state, and one after them
+    "ghosts": (table(3, [((1, 1, 0), (0, 1, 1)), ((1, 1, 0), (1, 1, 0)), ((0, 0, 2), (1, 1, 0)),
+                         ((0, 2, 0), (0, 2, 0))], [3, 5, 2, 7], 60), ("fixed", (20, 30, 10))),
+    # one to eight species, closed and open
+    "one": (open_network("birth", 70), ("fixed", (3,))),
+    "death": (open_network("death", 500), ("fixed", (400,))),
+    "predators": (open_network("lotka_volterra", 90), ("fixed", (40, 30))),
+    "wide2": (random_wide_network(4, 2, 100, 5), ("fixed", (50, 50))),
+    "wide5": (random_wide_network(3, 5, 300, 10), ("fixed", (60,) * 5)),
+    "wide8": (random_wide_network(9, 8, 64, 14), ("fixed", (8,) * 8)),
+    # caps that block firings most of the time
+    "capped4": (random_wide_network(6, 4, 9, 10, open_net=True), ("fixed", (9, 8, 9, 7))),
+    "capped7": (random_wide_network(12, 7, 30, 16, open_net=True), ("fixed", (29,) * 7)),
+}
+
+
+@pytest.mark.parametrize("word_bits", [0, 32], ids=["lanes", "words"])
+@pytest.mark.parametrize("name", sorted(GENERAL))
+def test_general_networks_on_both_kernels(torch, name, word_bits):
+    net, init = GENERAL[name]
+    M = 1000 + 7
+    print("case", name, word_bits, bwg.Network(net).quantized()["B"], flush=True)
+    e = bwg.Ensemble(bwg.Network(net), M, seed=4, net_id=9, word_bits=word_bits)
+    o = ssa.OracleEnsemble(net, M, seed=4, net_id=9)
+    t = 70.0 / bwg.Network(net).quantized()["Lambda"]
+    for x in (e, o):
+        x.init(init)
+        x.step(33)
+        x.advance(t)
+        x.advance(4 * t)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    ev, real = e.read_events()
+    np.testing.assert_array_equal(ev.cpu().numpy().astype(np.uint64), o.E)
+    want = np.zeros((M + 31) // 32, np.uint64)
+    np.add.at(want, np.arange(M) // 32, o.real.astype(np.uint64))
+    np.testing.assert_array_equal(real.cpu().numpy().astype(np.uint64), want)
