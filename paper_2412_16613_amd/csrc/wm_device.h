@@ -287,6 +287,16 @@ __device__ __forceinline__ void philox_planes(uint32_t (&n)[BC], uint64_t e, uin
 }
 
 
+// Lanes on which any plane is set.
+template <int W>
+__device__ __forceinline__ uint32_t any_plane(const uint32_t (&x)[W])
+{
+    uint32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) m |= x[q];
+    return m;
+}
+
 // Occupancies and per-replica event counts back to memory after a launch
 // that ran the word's events up to hi.
 template <int NB>
@@ -362,6 +372,13 @@ __device__ __forceinline__ void wm_word(const WmArgs &a, const uint64_t w)
         uint32_t actc = 0;
 
         for (uint64_t e = lo; e < hi; ++e) {
+            // states of total weight zero are left by no event: the rest of
+            // the chain is over once all of the wave's replicas are in one
+            // (the paper's network, N_tot = 64, 2^22 replicas, 20000 events
+            // with a shared threshold: 20.5 -> 1.5 ms)
+            if ((((uint32_t)e - (uint32_t)lo) & 63u) == 0 &&
+                !__any((any_plane(PAL) | any_plane(PAD) | any_plane(PLD) | any_plane(U)) != 0))
+                break;
             if (e >= nxt) actc = lane_mask_next(E, T, win.pend, e, win.blo, nxt);
             const uint32_t act = actc;
             // (a) threshold planes
@@ -462,6 +479,14 @@ __device__ __forceinline__ void wm_word_w(const WmArgs &a, const uint64_t t)
             actc[i] = 0;
         }
         for (uint64_t e = lo; e < hi; ++e) {
+            if ((((uint32_t)e - (uint32_t)lo) & 63u) == 0) {  // as in wm_word
+                uint32_t alive = 0;
+#pragma unroll
+                for (int i = 0; i < WPT; ++i)
+                    alive |= any_plane(PALs[i]) | any_plane(PADs[i]) | any_plane(PLDs[i]) |
+                             any_plane(Us[i]);
+                if (!__any(alive != 0)) break;
+            }
             uint32_t nsh[BC];
             if constexpr (SH) {
                 const uint32_t nv = nv_next;
@@ -549,6 +574,9 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v)
 // the events of half (s-1) mod 2, and a barrier separates the steps.  The
 // step count is the workgroup's largest window, so every wave meets every
 // barrier.  Results are those of wm_word.
+// Every 16 steps the consumers say whether any of their replicas can still
+// leave its state; once none can, all four waves end after the step's barrier.
+constexpr uint32_t kPcLook = 16;
 template <int NB, int BC, int FA, int CU, int PH, int FI = FA, int NT = 0, int BS = BC>
 __device__ __forceinline__ void wm_word_pc(const WmArgs &a, uint4 (*ring)[BC / 4][64],
                                            uint64_t *wave_span)
@@ -579,6 +607,7 @@ __device__ __forceinline__ void wm_word_pc(const WmArgs &a, uint4 (*ring)[BC / 4
     for (int i = 1; i < 4; ++i) span = wave_span[i] > span ? wave_span[i] : span;
     const uint64_t nsteps = (span + PH - 1) / PH;
     const int nq = (a.B + 3) / 4;
+    __syncthreads();  // the spans are read: words 2 and 3 now say who is alive
 
     if (producer) {
         const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
@@ -607,6 +636,7 @@ __device__ __forceinline__ void wm_word_pc(const WmArgs &a, uint4 (*ring)[BC / 4
                 }
             }
             __syncthreads();
+            if (s % kPcLook == 0 && !(wave_span[2] | wave_span[3])) break;
         }
         return;
     }
@@ -654,7 +684,13 @@ __device__ __forceinline__ void wm_word_pc(const WmArgs &a, uint4 (*ring)[BC / 4
                 }
             }
         }
+        if (s % kPcLook == 0) {
+            const bool alive = __any((any_plane(PAL) | any_plane(PAD) | any_plane(PLD) |
+                                      any_plane(U)) != 0);
+            if (lane == 0) wave_span[2 + grp] = alive ? 1 : 0;
+        }
         __syncthreads();
+        if (s % kPcLook == 0 && !(wave_span[2] | wave_span[3])) break;
     }
     if (valid) {
         if (lo < hi) a.real[w] += nreal;

@@ -253,3 +253,34 @@ def test_general_networks_on_both_kernels(torch, name, word_bits):
     want = np.zeros((M + 31) // 32, np.uint64)
     np.add.at(want, np.arange(M) // 32, o.real.astype(np.uint64))
     np.testing.assert_array_equal(real.cpu().numpy().astype(np.uint64), want)
+
+
+# ---- states that nothing leaves -----------------------------------------------------
+
+@pytest.mark.parametrize("kw", [dict(engine="lanes"), dict(word_bits=32), dict(block=256),
+                                dict(block=64), dict(word_bits=16), dict(word_bits=64),
+                                dict(shared_threshold=True),
+                                dict(shared_threshold=True, word_bits=64)],
+                         ids=lambda k: "-".join("%s" % v for v in k.values()))
+@pytest.mark.parametrize("M,n_tot,steps", [(65, 8, 700), (4000, 12, 900), (8192 + 3, 32, 3000)])
+def test_chains_that_end_early(torch, kw, M, n_tot, steps):
+    """The paper's network ends in states that no event leaves, at some event
+    of its own for every replica; loops that stop there still count every
+    event, and a later step finds nothing to do."""
+    net = paper_network(n_tot)
+    e = bwg.Ensemble(bwg.Network(net), M, seed=11, net_id=3, **kw)
+    draw = ssa.DRAW_SHARED if kw.get("shared_threshold") else ssa.DRAW_EVENT
+    o = ssa.OracleEnsemble(net, M, seed=11, net_id=3, draw=draw)
+    for x in (e, o):
+        x.init(("multinomial",))
+        x.step(steps // 7)
+        x.step(steps)
+    for more in (1, 500):
+        np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+        ev, real = e.read_events()
+        np.testing.assert_array_equal(ev.cpu().numpy().astype(np.uint64), o.E)
+        want = np.zeros((M + 31) // 32, np.uint64)
+        np.add.at(want, np.arange(M) // 32, o.real.astype(np.uint64))
+        np.testing.assert_array_equal(real.cpu().numpy().astype(np.uint64), want)
+        e.step(more)
+        o.step(more)
