@@ -110,6 +110,17 @@ __global__ void budget_kernel(const uint64_t *T, uint64_t len, int64_t k_lo, uin
     Et[i] = E[i] + K;
 }
 
+__global__ void fill_i32_kernel(int32_t *dst, uint64_t n, int32_t v, uint64_t i0)
+{
+    const uint64_t i = i0 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = v;
+}
+
+__global__ void store_ends_kernel(uint64_t *dst, RecEnds v, int n)
+{
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = v.v[threadIdx.x];
+}
+
 __global__ void add_u64_kernel(uint64_t *p, uint64_t v)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) p[0] += v;
@@ -277,6 +288,19 @@ hipError_t launch_budget(const uint64_t *T, uint64_t len, int64_t k_lo, uint64_t
         hipLaunchKernelGGL(budget_kernel, g, dim3(256), 0, s, T, len, k_lo, fixed_k, use_table,
                            seed, net_id, adv_dev, M, E, Et, i0);
     });
+}
+
+hipError_t launch_fill_i32(int32_t *p, uint64_t n, int32_t v, hipStream_t s)
+{
+    return launch_pieces(n, 256, [&](uint64_t i0, dim3 g) {
+        hipLaunchKernelGGL(fill_i32_kernel, g, dim3(256), 0, s, p, n, v, i0);
+    });
+}
+
+hipError_t launch_store_ends(uint64_t *dst, const RecEnds &v, int n, hipStream_t s)
+{
+    hipLaunchKernelGGL(store_ends_kernel, dim3(1), dim3(kRecEnds), 0, s, dst, v, n);
+    return hipGetLastError();
 }
 
 hipError_t launch_add_u64(uint64_t *p, uint64_t v, hipStream_t s)

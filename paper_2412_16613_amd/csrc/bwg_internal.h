@@ -78,6 +78,18 @@ struct WmArgs {
     uint32_t zs;            // shared threshold on [0, zs) for every replica (0: per replica)
     const uint32_t *ztab;   // shared thresholds of events [zbase, zbase + zlen)
     uint64_t zbase, zlen;
+    // recording (shared thresholds): after the launch's first rec_end[k]
+    // events, the counts of replicas rec_sel into rec_out[k][rec_n_sel][3] and
+    // rec_k0 + k into rec_first of replicas that newly have |N_L - N_D| at
+    // least rec_threshold (a null pointer: not asked for)
+    const uint64_t *rec_end;
+    const uint32_t *rec_sel;
+    int32_t *rec_out;
+    uint32_t *rec_first;
+    uint32_t rec_n;         // grid points (0: nothing recorded)
+    uint32_t rec_n_sel;
+    uint32_t rec_k0;
+    int32_t rec_threshold;
 };
 
 struct PlainArgs {
@@ -139,6 +151,12 @@ extern const int kGenVariantCount;
 
 hipError_t launch_plain(const PlainArgs &a, hipStream_t s, int block);
 hipError_t launch_wm_lanes(const WmArgs &a, hipStream_t s);
+// n <= kRecEnds values to dst (uint64), passed by value.
+constexpr int kRecEnds = 64;
+struct RecEnds {
+    uint64_t v[kRecEnds];
+};
+hipError_t launch_store_ends(uint64_t *dst, const RecEnds &v, int n, hipStream_t s);
 // Shared thresholds of events [e0, e0 + len) into tab (len uint32).
 hipError_t launch_shared_fill(uint32_t *tab, uint64_t e0, uint64_t len, uint64_t seed,
                               uint32_t net_id, uint32_t Z, hipStream_t s);
@@ -267,6 +285,7 @@ hipError_t launch_budget(const uint64_t *table, uint64_t len, int64_t k_lo,
                          uint32_t net_id, const uint64_t *advance_dev, uint64_t M,
                          const uint64_t *E, uint64_t *Etgt, hipStream_t s);
 hipError_t launch_add_u64(uint64_t *p, uint64_t v, hipStream_t s);
+hipError_t launch_fill_i32(int32_t *p, uint64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u64(uint64_t *p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_read_counts_planes(const uint32_t *planes, int S, int nb, uint64_t wp,
                                      uint64_t M, int32_t *dst, hipStream_t s);

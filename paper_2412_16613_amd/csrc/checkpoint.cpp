@@ -145,6 +145,10 @@ extern "C" int bwg_ensemble_save(bwg_ens *e, void *host_dst, uint64_t dst_bytes,
         return fail(BWG_ERANGE, "checkpoint needs %llu bytes, buffer holds %llu",
                     (unsigned long long)need, (unsigned long long)dst_bytes);
     hipStream_t s = (hipStream_t)stream;
+    if (e->zs) {  // the host keeps these replicas' one counter
+        HIP_TRY(launch_fill_u64(e->E, e->M, e->zE, s));
+        HIP_TRY(launch_fill_u64(e->Et, e->M, e->zE, s));
+    }
     uint8_t *dst = (uint8_t *)host_dst;
     uint64_t h[kHeaderWords] = {};
     h[0] = kMagic;

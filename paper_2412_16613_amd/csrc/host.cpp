@@ -978,7 +978,8 @@ void bwg::note_ran(bwg_ens *e, uint64_t max_events)
 
 // One launch of the pending events of every word, at most max_events each
 // (0: all of them).
-static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s)
+static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s,
+                         const WmArgs *rec = nullptr)
 {
     const bwg_net *n = e->net;
     if (e->engine != BWG_ENGINE_PLAIN) {
@@ -1002,7 +1003,17 @@ static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s)
         a.ztab = (const uint32_t *)e->table;
         a.zbase = e->zbase;
         a.zlen = e->zs ? e->zlen : 0;
-        if (a.zs && !a.zlen) return fail(BWG_EINVAL, "shared thresholds not staged");
+        if (a.zs && !a.zlen && !rec) return fail(BWG_EINVAL, "shared thresholds not staged");
+        if (rec) {
+            a.rec_end = rec->rec_end;
+            a.rec_sel = rec->rec_sel;
+            a.rec_out = rec->rec_out;
+            a.rec_first = rec->rec_first;
+            a.rec_n = rec->rec_n;
+            a.rec_n_sel = rec->rec_n_sel;
+            a.rec_k0 = rec->rec_k0;
+            a.rec_threshold = rec->rec_threshold;
+        }
         const bool lanes = e->engine == BWG_ENGINE_LANES || words_on_lanes(e);
         const bool frank_jit = !lanes && e->want_jit_frank && e->block <= 0;
         if (frank_jit && !e->jit_frank) {
@@ -1151,9 +1162,6 @@ int bwg::schedule_ensemble(bwg_ens *e, double t_end, hipStream_t s, uint64_t *km
             if (rc) return rc;
             K = shared_budget(e, t);
         }
-        HIP_TRY(launch_budget(nullptr, 0, 0, K, 0, e->seed, e->net_id, e->adv_dev, e->M, e->E,
-                              e->Et, s));
-        HIP_TRY(launch_add_u64(e->adv_dev, 1, s));
         e->t_now = t_end;
         e->adv += 1;
         *kmin_out = *kmax_out = K;
@@ -1242,8 +1250,9 @@ extern "C" int bwg_ensemble_step(bwg_ens *e, uint64_t n_events, void *stream)
     }
     if (e->zs && e->pending)
         return fail(BWG_EINVAL, "shared thresholds: run the pending events first");
-    HIP_TRY(launch_budget(nullptr, 0, 0, n_events, 0, e->seed, e->net_id, e->adv_dev, e->M, e->E,
-                          e->Et, s));
+    if (!e->zs)
+        HIP_TRY(launch_budget(nullptr, 0, 0, n_events, 0, e->seed, e->net_id, e->adv_dev, e->M,
+                              e->E, e->Et, s));
     note_scheduled(e, n_events, n_events);
     return run_events(e, s);
 }
@@ -1274,6 +1283,69 @@ extern "C" int bwg_ensemble_histogram(bwg_ens *e, int32_t n_bins, uint64_t *dst,
     return BWG_OK;
 }
 
+// Recording of a shared-threshold ensemble: the budget of every grid point is
+// the host's own draw, so one launch runs the events of as many points as the
+// table holds thresholds for and records after each of them, with the state in
+// registers (a launch per point, its first-passage and gather kernels and the
+// budgets took 0.17 ms a point at 2^22 replicas, ten events of which are
+// 0.01).  A point of more events than the table holds runs in launches of its
+// own before the recording one, which then has none left for it.
+static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, const WmArgs &what,
+                         hipStream_t s)
+{
+    // the table region: thresholds, then up to ends grid points
+    const uint32_t ends = (uint32_t)std::min<uint64_t>(n_points, e->table_cap / 4);
+    const uint64_t cap = (e->table_cap - ends) * 2;
+    uint64_t *dev_end = e->table + (e->table_cap - ends);
+    uint32_t k = 0;
+    while (k < n_points) {
+        std::vector<uint64_t> end;
+        uint64_t len = 0;
+        const uint32_t first = k;
+        while (k < n_points && end.size() < ends) {
+            uint64_t kmin, kmax;
+            const double t0 = e->t_now;
+            int rc = schedule_ensemble(e, t_grid[k], s, &kmin, &kmax);
+            if (rc) return rc;
+            if (len + kmax > cap) {
+                if (!end.empty()) {  // the next launch draws and takes this point
+                    e->t_now = t0;
+                    e->adv -= 1;
+                    break;
+                }
+                note_scheduled(e, kmin, kmax);
+                rc = run_shared(e, 0, s);
+                if (rc) return rc;
+                kmax = 0;
+            }
+            len += kmax;
+            end.push_back(len);
+            ++k;
+        }
+        for (size_t i = 0; i < end.size(); i += kRecEnds) {
+            RecEnds v{};
+            const int n = (int)std::min<size_t>(kRecEnds, end.size() - i);
+            for (int j = 0; j < n; ++j) v.v[j] = end[i + j];
+            HIP_TRY(launch_store_ends(dev_end + i, v, n, s));
+        }
+        if (len)
+            HIP_TRY(launch_shared_fill((uint32_t *)e->table, e->zE, len, e->seed, e->net_id,
+                                       e->zs, s));
+        WmArgs rec = what;
+        rec.rec_end = dev_end;
+        rec.rec_n = (uint32_t)end.size();
+        rec.rec_k0 = first;
+        if (rec.rec_out) rec.rec_out += (uint64_t)first * rec.rec_n_sel * 3;
+        e->zbase = e->zE;
+        e->zlen = len;
+        note_scheduled(e, len, len);
+        const int rc = launch_events(e, len, s, &rec);
+        if (rc) return rc;
+        e->zE += len;
+    }
+    return BWG_OK;
+}
+
 extern "C" int bwg_ensemble_record(bwg_ens *e, const double *t_grid, uint32_t n_points,
                                    const uint32_t *dev_sel, uint32_t n_sel, int32_t *dev_out,
                                    int32_t threshold, uint32_t *dev_first, void *stream)
@@ -1295,6 +1367,19 @@ extern "C" int bwg_ensemble_record(bwg_ens *e, const double *t_grid, uint32_t n_
         t = t_grid[k];
     }
     hipStream_t s = (hipStream_t)stream;
+    // every wave looks through the selection once (1024 entries: a few us)
+    if (e->zs && e->engine == BWG_ENGINE_BITWISE && e->word_bits == 32 && !e->epl && n_points &&
+        n_sel <= 1024 && !e->pending && e->table_cap >= 8) {
+        // an index past the last replica reads -1
+        if (n_sel) HIP_TRY(launch_fill_i32(dev_out, 3ull * n_sel * n_points, -1, s));
+        WmArgs what{};
+        what.rec_sel = dev_sel;
+        what.rec_out = dev_out;
+        what.rec_n_sel = n_sel;
+        what.rec_first = dev_first;
+        what.rec_threshold = threshold;
+        return record_shared(e, t_grid, n_points, what, s);
+    }
     const uint32_t *planes = e->engine != BWG_ENGINE_PLAIN ? e->planes : nullptr;
     for (uint32_t k = 0; k < n_points; ++k) {
         const int rc = bwg_ensemble_advance(e, t_grid[k], stream);
@@ -1313,7 +1398,10 @@ extern "C" int bwg_ensemble_read_events(bwg_ens *e, uint64_t *dev_events, uint64
 {
     if (!e) return fail(BWG_EINVAL, "null ensemble");
     hipStream_t s = (hipStream_t)stream;
-    if (dev_events) HIP_TRY(launch_copy_u64(e->E, dev_events, e->M, s));
+    if (dev_events && e->zs)
+        HIP_TRY(launch_fill_u64(dev_events, e->M, e->zE, s));
+    else if (dev_events)
+        HIP_TRY(launch_copy_u64(e->E, dev_events, e->M, s));
     if (dev_real) {
         if (e->engine != BWG_ENGINE_PLAIN)
             HIP_TRY(launch_copy_u64(e->real, dev_real, (e->M + 31) / 32, s));
@@ -1328,7 +1416,7 @@ extern "C" int bwg_ensemble_stats(bwg_ens *e, void *stream, bwg_stats *out)
     TraceRange trace_("bwg_ensemble_stats");
     if (!e || !out) return fail(BWG_EINVAL, "null argument");
     hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(launch_sum_u64(e->E, e->M, e->scratch, 0, s));
+    if (!e->zs) HIP_TRY(launch_sum_u64(e->E, e->M, e->scratch, 0, s));
     HIP_TRY(launch_sum_u64(e->real, e->engine != BWG_ENGINE_PLAIN ? (e->M + 31) / 32 : e->M,
                            e->scratch, 1, s));
     uint64_t h[2];
@@ -1337,7 +1425,7 @@ extern "C" int bwg_ensemble_stats(bwg_ens *e, void *stream, bwg_stats *out)
     out->n_replicas = e->M;
     out->advance_index = e->adv;
     out->t_now = e->t_now;
-    out->events_total = h[0];
+    out->events_total = e->zs ? e->M * e->zE : h[0];  // one counter for all replicas
     out->real_total = h[1];
     return BWG_OK;
 }

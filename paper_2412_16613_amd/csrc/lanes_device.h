@@ -450,24 +450,24 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
 }
 
 // The same for shared thresholds: at every event all replicas compare the n
-// that the table holds.
+// that the table holds (one event counter for all of them, kept by the host).
 template <class Replica>
 __device__ __forceinline__ void wm_lanes_shared(const WmArgs &a, uint64_t w)
 {
     const int l = threadIdx.x & 31;
     const int hv = (threadIdx.x >> 5) & 1;
     if (w >= a.n_words) return;
-    const LaneWindow v = lane_window(a, 32 * w + (uint64_t)l);
+    const bool live = 32 * w + (uint64_t)l < a.M;
+    LaneWindow v{};  // not live: no counter is stored
     Replica rep(a);
     uint32_t N[Replica::S];
     unpack_counts(a, w, l, N);
     rep.set_counts(N);
     uint32_t nreal = 0;
-    for (uint64_t e = v.lo; e < v.hi; ++e) {
+    for (uint64_t e = a.zbase; e < a.zbase + a.zlen; ++e) {
         const uint32_t n = shared_at(a, e);
-        const bool on = v.mine && v.E0 <= e && e < v.T0;
-        nreal += on && n < rep.total() ? 1u : 0u;
-        rep.fire(n, on, 0);
+        nreal += live && n < rep.total() ? 1u : 0u;
+        rep.fire(n, live, 0);
     }
     for (int o = 16; o; o >>= 1) nreal += (uint32_t)__shfl_xor((int)nreal, o, 32);
     rep.get_counts(N);

@@ -297,12 +297,10 @@ __device__ __forceinline__ uint32_t any_plane(const uint32_t (&x)[W])
     return m;
 }
 
-// Occupancies and per-replica event counts back to memory after a launch
-// that ran the word's events up to hi.
+// Occupancies of word w back to memory.
 template <int NB>
-__device__ __forceinline__ void store_word(const WmArgs &a, uint64_t w, uint32_t live,
-                                           uint64_t hi, const uint32_t (&L)[NB],
-                                           const uint32_t (&D)[NB], const uint32_t (&A)[NB])
+__device__ __forceinline__ void store_planes(const WmArgs &a, uint64_t w, const uint32_t (&L)[NB],
+                                             const uint32_t (&D)[NB], const uint32_t (&A)[NB])
 {
     uint32_t *po = a.planes;
     const int nbm = a.nb_mem;
@@ -314,6 +312,16 @@ __device__ __forceinline__ void store_word(const WmArgs &a, uint64_t w, uint32_t
             po[((uint64_t)2 * nbm + q) * a.wp + w] = A[q];
         }
     }
+}
+
+// Occupancies and per-replica event counts back to memory after a launch
+// that ran the word's events up to hi.
+template <int NB>
+__device__ __forceinline__ void store_word(const WmArgs &a, uint64_t w, uint32_t live,
+                                           uint64_t hi, const uint32_t (&L)[NB],
+                                           const uint32_t (&D)[NB], const uint32_t (&A)[NB])
+{
+    store_planes<NB>(a, w, L, D, A);
     uint64_t *Ew = a.E + 32 * w;
     const uint64_t *T = a.Etgt + 32 * w;
     for (int l = 0; l < 32; ++l) {
@@ -329,6 +337,104 @@ __device__ __forceinline__ uint32_t live_lanes(const WmArgs &a, uint64_t w)
     return rem >= 32 ? 0xFFFFFFFFu : ((1u << rem) - 1u);
 }
 
+// Lanes with x >= K, K the same for every lane: the complement of the borrow
+// of x - K (K < 2^W).
+template <int W>
+__device__ __forceinline__ uint32_t geq_uniform(const uint32_t (&x)[W], uint32_t K)
+{
+    uint32_t br = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+        br = BWG_OP3(x[q], (uint32_t)((int32_t)(K << (31 - q)) >> 31), br, L_BORROW);
+    return ~br;
+}
+
+// Lanes with |L - D| >= K (K >= 0): L - D + 2^NB in NB + 1 planes against
+// 2^NB + K from above and 2^NB - K from below.
+template <int NB>
+__device__ __forceinline__ uint32_t apart_by(const uint32_t (&L)[NB], const uint32_t (&D)[NB],
+                                             int32_t K)
+{
+    if (K > (1 << NB) - 1) return 0;
+    if (K <= 0) return ~0u;
+    uint32_t x[NB + 1], c = ~0u;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        x[q] = BWG_OP3(L[q], ~D[q], c, L_XOR3);
+        c = BWG_OP3(L[q], ~D[q], c, L_MAJ);
+    }
+    x[NB] = c;
+    return geq_uniform<NB + 1>(x, (1u << NB) + (uint32_t)K) |
+           ~geq_uniform<NB + 1>(x, (1u << NB) - (uint32_t)K + 1u);
+}
+
+// What a recording launch keeps of a word: the lanes whose first passage is
+// already noted, and where in the selection its replicas are.
+struct WordRecord {
+    uint32_t seen;
+    uint32_t j0, j1;  // selected replicas of the word are among [j0, j1)
+};
+
+// Every lane of the wave takes part (its word may lie past the end): the 32
+// entries of the wave's 64 words are read 64 at a time.
+__device__ __forceinline__ WordRecord record_begin(const WmArgs &a, uint64_t w, bool valid)
+{
+    WordRecord r{0u, 0u, 0u};
+    const uint32_t lane = threadIdx.x & 63;
+    if (a.rec_first) {
+        const uint64_t i0 = 32 * (w - lane) + lane;
+        for (uint32_t k = 0; k < 32; ++k) {
+            const uint64_t i = i0 + 64 * k;
+            const uint64_t m = __ballot(i < a.M && a.rec_first[i < a.M ? i : 0] != 0xFFFFFFFFu);
+            if (lane >> 1 == k) r.seen = (lane & 1) ? (uint32_t)(m >> 32) : (uint32_t)m;
+        }
+    }
+    if (valid) {
+        for (uint32_t j = 0; j < a.rec_n_sel; ++j) {
+            if (a.rec_sel[j] >> 5 == w) {
+                if (r.j0 == r.j1) r.j0 = j;
+                r.j1 = j + 1;
+            }
+        }
+    }
+    return r;
+}
+
+template <int NB>
+__device__ __forceinline__ void record_point(const WmArgs &a, uint64_t w, uint32_t live,
+                                             uint32_t k, WordRecord &r, const uint32_t (&L)[NB],
+                                             const uint32_t (&D)[NB], const uint32_t (&A)[NB])
+{
+    if (a.rec_first) {
+        uint32_t hit = apart_by<NB>(L, D, a.rec_threshold) & live & ~r.seen;
+        r.seen |= hit;
+        while (hit) {
+            a.rec_first[32 * w + (uint32_t)__builtin_ctz(hit)] = a.rec_k0 + k;
+            hit &= hit - 1;
+        }
+    }
+    for (uint32_t j = r.j0; j < r.j1; ++j) {
+        const uint32_t i = a.rec_sel[j];
+        if (i >> 5 != w || !((live >> (i & 31)) & 1u)) continue;
+        int32_t c[3] = {0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            c[0] |= (int32_t)((L[q] >> (i & 31)) & 1u) << q;
+            c[1] |= (int32_t)((D[q] >> (i & 31)) & 1u) << q;
+            c[2] |= (int32_t)((A[q] >> (i & 31)) & 1u) << q;
+        }
+        int32_t *dst = a.rec_out + 3 * ((uint64_t)k * a.rec_n_sel + j);
+        dst[0] = c[0];
+        dst[1] = c[1];
+        dst[2] = c[2];
+    }
+}
+
+// Shared thresholds (SH below): the replicas move in lockstep, so a launch
+// runs the events [zbase, zbase + zlen) of the table on every live lane, and
+// the host keeps the one event counter (E and Etgt are neither read nor
+// written: at 2^22 replicas their scan was 0.1 ms of every launch).
+//
 // One word (32 replicas) of an ensemble: run its pending events.
 // NB count planes, BC = 4 * (quads of threshold planes), FA product shift
 // of the A + L and A + D weights and FI that of the L + D weight (-1: run
@@ -342,18 +448,24 @@ __device__ __forceinline__ void wm_word(const WmArgs &a, const uint64_t w)
     constexpr bool EXACT = Sh::EXACT;
     constexpr int WP = Sh::WP, WD = Sh::WD, UW = Sh::UW, FMIN = Sh::FMIN;
     constexpr int WD_AL = Sh::WD_AL, WD_QA = Sh::WD_QA, WD_LD = Sh::WD_LD;
-    if (w >= a.n_words) return;
+    const bool valid = w < a.n_words;
+    WordRecord rec{};
+    if constexpr (SH) {
+        if (a.rec_n) rec = record_begin(a, w, valid);
+    }
+    if (!valid) return;
 
     const uint32_t live = live_lanes(a, w);
     const uint64_t *E = a.E + 32 * w;
     const uint64_t *T = a.Etgt + 32 * w;
-    const WordWindow win = word_window(a, E, T, live);
+    WordWindow win{a.zbase, a.zbase + a.zlen, 0, 0, 0u};
+    if constexpr (!SH) win = word_window(a, E, T, live);
     const uint64_t lo = win.lo, hi = win.hi;
 
     uint32_t L[NB], D[NB], A[NB];
     load_word<NB>(a, w, L, D, A);
 
-    if (lo < hi) {
+    if (lo < hi || (SH && a.rec_n)) {
         uint32_t PAL[WP], PAD[WP], PLD[WP], U[UW];
         const uint32_t cu = CU >= 0 ? (uint32_t)CU : a.cu;
         init_weights<NB, UW, WP, EXACT>(L, D, A, cu, PAL, PAD, PLD, U);
@@ -366,39 +478,58 @@ __device__ __forceinline__ void wm_word(const WmArgs &a, const uint64_t w)
         uint32_t lastm[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) lastm[j] = (4 * (nq - 1) + j < a.B) ? ~0u : 0u;
-        uint32_t nv_next = SH ? shared_at(a, lo) : 0u;
+        uint32_t nv_next = SH && lo < hi ? shared_at(a, lo) : 0u;
         uint64_t nreal = 0;
         uint64_t nxt = 0;  // next event at which the active lanes change
         uint32_t actc = 0;
 
-        for (uint64_t e = lo; e < hi; ++e) {
-            // states of total weight zero are left by no event: the rest of
-            // the chain is over once all of the wave's replicas are in one
-            // (the paper's network, N_tot = 64, 2^22 replicas, 20000 events
-            // with a shared threshold: 20.5 -> 1.5 ms)
-            if ((((uint32_t)e - (uint32_t)lo) & 63u) == 0 &&
-                !__any((any_plane(PAL) | any_plane(PAD) | any_plane(PLD) | any_plane(U)) != 0))
-                break;
-            if (e >= nxt) actc = lane_mask_next(E, T, win.pend, e, win.blo, nxt);
-            const uint32_t act = actc;
-            // (a) threshold planes
-            uint32_t n[BC];
-            if constexpr (SH) {
-                // one n for every replica: plane q is all ones where bit q is
-                // set; the next event's n is loaded while this one runs
-                const uint32_t nv = nv_next;
-                if (e + 1 < hi) nv_next = shared_at(a, e + 1);
+        // a recording launch stops at each of its grid points
+        const uint32_t n_seg = SH && a.rec_n ? a.rec_n : 1u;
+        uint64_t e = lo;
+        bool over = false;
+        for (uint32_t seg = 0; seg < n_seg; ++seg) {
+            const uint64_t stop = SH && a.rec_n ? lo + a.rec_end[seg] : hi;
+            for (; e < stop && !over; ++e) {
+                // states of total weight zero are left by no event: the rest of
+                // the chain is over once all of the wave's replicas are in one
+                // (the paper's network, N_tot = 64, 2^22 replicas, 20000 events
+                // with a shared threshold: 20.5 -> 1.5 ms)
+                if ((((uint32_t)e - (uint32_t)lo) & 63u) == 0 &&
+                    !__any((any_plane(PAL) | any_plane(PAD) | any_plane(PLD) | any_plane(U)) !=
+                           0)) {
+                    over = true;
+                    break;
+                }
+                uint32_t act = live;
+                if constexpr (!SH) {
+                    if (e >= nxt) actc = lane_mask_next(E, T, win.pend, e, win.blo, nxt);
+                    act = actc;
+                }
+                // (a) threshold planes
+                uint32_t n[BC];
+                if constexpr (SH) {
+                    // one n for every replica: plane q is all ones where bit q is
+                    // set; the next event's n is loaded while this one runs
+                    const uint32_t nv = nv_next;
+                    if (e + 1 < hi) nv_next = shared_at(a, e + 1);
 #pragma unroll
-                for (int q = 0; q < BC; ++q)
-                    n[q] = q < 32 ? (uint32_t)((int32_t)(nv << (31 - q)) >> 31) : 0u;
-            } else {
-                philox_planes<BC>(n, e, G, a.net_id, k0, k1, nq, lastm);
-            }
+                    for (int q = 0; q < BC; ++q)
+                        n[q] = q < 32 ? (uint32_t)((int32_t)(nv << (31 - q)) >> 31) : 0u;
+                } else {
+                    philox_planes<BC>(n, e, G, a.net_id, k0, k1, nq, lastm);
+                }
 #include "wm_event_body.inc"
+            }
+            if constexpr (SH) {
+                if (a.rec_n) record_point<NB>(a, w, live, seg, rec, L, D, A);
+            }
         }
         a.real[w] += nreal;
     }
-    store_word<NB>(a, w, live, hi, L, D, A);
+    if constexpr (SH)
+        store_planes<NB>(a, w, L, D, A);
+    else
+        store_word<NB>(a, w, live, hi, L, D, A);
 }
 
 // Word widths other than 32 replicas per thread (WW = 16 or 64); the
@@ -434,8 +565,11 @@ __device__ __forceinline__ void wm_word_w(const WmArgs &a, const uint64_t t)
         uint32_t lv = valid ? live_lanes(a, wv[i]) : 0u;
         if (WW == 16) lv &= (t & 1) ? 0xFFFF0000u : 0x0000FFFFu;
         livev[i] = lv;
-        win[i] = word_window(a, a.E + 32 * (valid ? wv[i] : 0), a.Etgt + 32 * (valid ? wv[i] : 0),
-                             lv);
+        if constexpr (SH)
+            win[i] = WordWindow{a.zbase, a.zbase + (lv ? a.zlen : 0), 0, 0, 0u};
+        else
+            win[i] = word_window(a, a.E + 32 * (valid ? wv[i] : 0),
+                                 a.Etgt + 32 * (valid ? wv[i] : 0), lv);
         if (win[i].lo < win[i].hi) {
             lo = win[i].lo < lo ? win[i].lo : lo;
             hi = win[i].hi > hi ? win[i].hi : hi;
@@ -470,7 +604,7 @@ __device__ __forceinline__ void wm_word_w(const WmArgs &a, const uint64_t t)
         uint32_t lastm[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) lastm[j] = (4 * (nq - 1) + j < a.B) ? ~0u : 0u;
-        uint32_t nv_next = SH ? shared_at(a, lo) : 0u;
+        uint32_t nv_next = SH && lo < hi ? shared_at(a, lo) : 0u;
         uint64_t nxt[WPT];
         uint32_t actc[WPT];
 #pragma unroll
@@ -497,10 +631,14 @@ __device__ __forceinline__ void wm_word_w(const WmArgs &a, const uint64_t t)
             }
 #pragma unroll
             for (int i = 0; i < WPT; ++i) {
-                const uint64_t *E = a.E + 32 * wv[i];
-                const uint64_t *T = a.Etgt + 32 * wv[i];
-                if (e >= nxt[i]) actc[i] = lane_mask_next(E, T, win[i].pend, e, win[i].blo, nxt[i]);
-                const uint32_t act = actc[i];
+                uint32_t act = livev[i];
+                if constexpr (!SH) {
+                    const uint64_t *E = a.E + 32 * wv[i];
+                    const uint64_t *T = a.Etgt + 32 * wv[i];
+                    if (e >= nxt[i])
+                        actc[i] = lane_mask_next(E, T, win[i].pend, e, win[i].blo, nxt[i]);
+                    act = actc[i];
+                }
                 uint32_t n[BC];
                 if constexpr (SH) {
 #pragma unroll
@@ -537,17 +675,22 @@ __device__ __forceinline__ void wm_word_w(const WmArgs &a, const uint64_t t)
                     ph[(((uint64_t)2 * nbm + q) * a.wp + w) * 2 + (t & 1)] = (uint16_t)(As[i][q] >> sh);
                 }
             }
-            uint64_t *Ew = a.E + 32 * w;
-            const uint64_t *T = a.Etgt + 32 * w;
-            for (int l = 0; l < 32; ++l) {
-                if (!((livev[i] >> l) & 1u)) continue;
-                const uint64_t x = Ew[l], y = T[l];
-                Ew[l] = hi < x ? x : (hi > y ? y : hi);
+            if constexpr (!SH) {
+                uint64_t *Ew = a.E + 32 * w;
+                const uint64_t *T = a.Etgt + 32 * w;
+                for (int l = 0; l < 32; ++l) {
+                    if (!((livev[i] >> l) & 1u)) continue;
+                    const uint64_t x = Ew[l], y = T[l];
+                    Ew[l] = hi < x ? x : (hi > y ? y : hi);
+                }
             }
             if (nrealv[i]) atomicAdd((unsigned long long *)&a.real[w], (unsigned long long)nrealv[i]);
         } else {
             if (win[i].lo < win[i].hi) a.real[w] += nrealv[i];
-            store_word<NB>(a, w, livev[i], hi, Ls[i], Ds[i], As[i]);
+            if constexpr (SH)
+                store_planes<NB>(a, w, Ls[i], Ds[i], As[i]);
+            else
+                store_word<NB>(a, w, livev[i], hi, Ls[i], Ds[i], As[i]);
         }
     }
 }

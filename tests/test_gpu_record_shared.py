@@ -1,0 +1,111 @@
+"""Recording shared-threshold ensembles: one launch runs the events of many
+grid points and records in between.  Exact against the oracle advanced through
+the same grid, where launches are cut (small tables, points of more events than
+a table holds, points without events), at every selection and threshold."""
+
+import numpy as np
+import pytest
+
+import paper_2412_16613_amd as bwg
+from oracle import ssa
+from workloads import frank_network, paper_network
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+def check(torch, net, M, grid, sel, threshold, first=None, init=("multinomial",), before=0, **kw):
+    print("case", net["n_tot"], M, len(grid), len(sel), threshold, kw, flush=True)
+    e = bwg.Ensemble(bwg.Network(net), M, seed=3, net_id=5, shared_threshold=True, **kw)
+    o = ssa.OracleEnsemble(net, M, seed=3, net_id=5, draw=ssa.DRAW_SHARED)
+    for x in (e, o):
+        x.init(init)
+        x.step(before)
+    want_first = np.full(M, -1, np.int64) if first is None else first.copy()
+    f0 = None if first is None else torch.tensor(first, dtype=torch.int64)
+    traj, got_first = e.record(grid, sel, threshold=threshold, first=f0)
+    want = np.zeros((len(grid), len(sel), 3), np.int32)
+    for k, t in enumerate(grid):
+        o.advance(t)
+        for j, i in enumerate(sel):
+            want[k, j] = o.counts[i] if i < M else -1
+        d = np.abs(o.counts[:, 0].astype(np.int64) - o.counts[:, 1])
+        if threshold is not None:
+            want_first[(want_first < 0) & (d >= threshold)] = k
+    np.testing.assert_array_equal(traj.cpu().numpy(), want)
+    if threshold is not None:
+        np.testing.assert_array_equal(got_first.cpu().numpy(), want_first)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    ev, real = e.read_events()
+    np.testing.assert_array_equal(ev.cpu().numpy().astype(np.uint64), o.E)
+    s = e.stats()
+    assert s["events_total"] == int(o.E.sum()) and s["real_total"] == int(o.real.sum())
+    # and the ensemble goes on as if it had been advanced
+    e.step(70)
+    o.step(70)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+
+
+GRID = list(np.linspace(0.02, 0.5, 23))
+
+
+# a table of 8 entries: 2 grid points and 12 thresholds a launch, so that most
+# points are cut off and those of more than 12 events run beforehand
+@pytest.mark.parametrize("cap", [8, 24, 100, 0])
+@pytest.mark.parametrize("M", [1, 64, 65, 4096 + 33])
+def test_launches_cut_by_the_table(torch, cap, M):
+    check(torch, paper_network(12), M, GRID, [0, M - 1, M, 10 ** 9], 7, table_capacity=cap)
+
+
+@pytest.mark.parametrize("threshold", [0, 1, 15, 31, 32, 33, 63, 64, 10 ** 6, None])
+def test_thresholds(torch, threshold):
+    check(torch, paper_network(32), 500, GRID, [3], threshold)
+
+
+def test_selections(torch):
+    net = paper_network(20)
+    check(torch, net, 300, GRID, [], 9)
+    check(torch, net, 300, GRID, [7] * 5 + [8, 40, 7, 299, 300], 9)
+    check(torch, net, 300, GRID, list(range(300)) * 3, 9)              # 900 of at most 1024
+    check(torch, net, 300, GRID[:5], list(range(300)) * 4, 9)          # a launch per point
+
+
+@pytest.mark.parametrize("kw", [dict(block=64), dict(block=256), dict(word_bits=32),
+                                dict(word_bits=64), dict(engine="lanes"), dict(jit=False),
+                                dict(events_per_launch=5)],
+                         ids=lambda k: "%s" % list(k.values())[0])
+def test_engines_and_options(torch, kw):
+    check(torch, paper_network(32), 777, GRID, [0, 31, 32, 776], 24, before=5, **kw)
+
+
+def test_compiled_network_and_conversions(torch):
+    net = frank_network(90, k0=0.03)       # no precompiled weights
+    check(torch, net, 2000, [0.0, 0.3, 0.3, 0.9, 2.5, 9.0], [0, 1999], 40,
+          init=("fixed", (0, 0, 90)))
+    check(torch, net, 2000, [0.5, 3.0], [77], 40, init=("fixed", (0, 0, 90)), jit=False)
+
+
+def test_first_passages_carried_on(torch):
+    M = 130
+    first = np.full(M, -1, np.int64)
+    first[::3] = 2
+    check(torch, paper_network(16), M, GRID, [1], 8, first=first)
+
+
+def test_checkpoint_of_a_recorded_ensemble(torch):
+    net = paper_network(24)
+    a = bwg.Ensemble(bwg.Network(net), 333, seed=1, shared_threshold=True)
+    a.init_multinomial()
+    a.record(GRID[:9], [0], threshold=10)
+    b = bwg.Ensemble(bwg.Network(net), 333, seed=1, shared_threshold=True)
+    b.restore(a.save())
+    for x in (a, b):
+        x.advance(0.6)
+    np.testing.assert_array_equal(a.read_counts().cpu().numpy(), b.read_counts().cpu().numpy())
+    np.testing.assert_array_equal(a.read_events()[0].cpu().numpy(), b.read_events()[0].cpu().numpy())
