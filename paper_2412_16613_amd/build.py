@@ -50,8 +50,8 @@ def _compile(src):
 
 
 # Headers of the device code that the run-time compiled kernels include.
-JIT_HEADERS = ("bitops.h", "bwg_internal.h", "wm_device.h", "wm_event_body.inc", "lanes_device.h",
-               "gen_device.h")
+JIT_HEADERS = ("bitops.h", "bwg_internal.h", "wm_device.h", "wm_event_body.inc", "event_draw.h",
+               "lanes_device.h", "gen_device.h")
 
 
 # The run-time compiler has the device builtins but no runtime header: the

@@ -223,6 +223,8 @@ struct LatShape {
     uint64_t Wsite;         // W_R + 4 W_H
     uint64_t C;             // S Wsite
     uint64_t thresh;        // 2^64 mod C
+    uint32_t inv_lx;        // ceil(2^24 / lx)
+    uint32_t pad;
 };
 
 struct LatArgs {

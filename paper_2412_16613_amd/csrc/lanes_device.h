@@ -30,6 +30,7 @@
 // 6.2 for 16523 replicas of 4 10^4 events of which 42 % are real.
 #pragma once
 
+#include "event_draw.h"
 #include "wm_device.h"
 
 namespace bwg {
@@ -84,61 +85,6 @@ __device__ __forceinline__ void transpose8(uint32_t *x)
         x[k + 1] = ((lo >> 1) & 0x55555555u) | (hi & 0xAAAAAAAAu);
     }
 }
-
-// EVENT planes of one event of a word: the NQ Philox calls differ in one
-// counter word only, so the first rounds share work.  Round 1's products and
-// the product on counter word 0 of round 2 depend on the word and the call,
-// not on the event (up to its high bits): ha, la hold the latter.  The other
-// products of rounds 1 and 2 and one of round 3 are the same for all calls.
-template <int NQ>
-struct EventDraw {
-    static constexpr int OFF = LanesRow<NQ>::SH;  // plane p goes to x[OFF + p]
-    uint32_t k0, k1, net_id, G;
-    uint32_t ha[NQ], la[NQ];
-
-    __device__ __forceinline__ void set_word(uint32_t hi)
-    {
-        const uint32_t h = (uint32_t)(((uint64_t)0xCD9E8D57u * G) >> 32);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const uint32_t c1 = (DOM_EVENT << 24) | ((uint32_t)q << 16) | hi;
-            const uint64_t p = (uint64_t)0xD2511F53u * (uint32_t)BWG_OP3(h, c1, k0, L_XOR3);
-            ha[q] = (uint32_t)(p >> 32);
-            la[q] = (uint32_t)p;
-        }
-    }
-    __device__ __forceinline__ void draw(uint32_t e_lo, uint32_t (&x)[32]) const
-    {
-        constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
-        constexpr uint64_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
-        // shared by the calls
-        const uint64_t a0 = M0 * e_lo;                                           // round 1
-        const uint64_t a1 = M1 * (uint32_t)BWG_OP3((uint32_t)(a0 >> 32), net_id, k1, L_XOR3);  // round 2
-        const uint32_t lg = (uint32_t)(M1 * G);
-        const uint64_t a2 = M0 * (uint32_t)BWG_OP3((uint32_t)(a1 >> 32), lg, k0 + W0, L_XOR3);  // round 3
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            // counter word 2 after round 2, then round 3
-            const uint64_t b = M1 * (uint32_t)BWG_OP3(ha[q], (uint32_t)a0, k1 + W1, L_XOR3);
-            uint32_t c0 = BWG_OP3((uint32_t)(b >> 32), (uint32_t)a1, k0 + 2 * W0, L_XOR3);
-            uint32_t c1 = (uint32_t)b;
-            uint32_t c2 = BWG_OP3((uint32_t)(a2 >> 32), la[q], k1 + 2 * W1, L_XOR3);
-            uint32_t c3 = (uint32_t)a2;
-#pragma unroll
-            for (int r = 3; r < 10; ++r) {
-                const uint64_t p0 = M0 * c0, p1 = M1 * c2;
-                c0 = BWG_OP3((uint32_t)(p1 >> 32), c1, k0 + (uint32_t)r * W0, L_XOR3);
-                c2 = BWG_OP3((uint32_t)(p0 >> 32), c3, k1 + (uint32_t)r * W1, L_XOR3);
-                c1 = (uint32_t)p1;
-                c3 = (uint32_t)p0;
-            }
-            x[OFF + 4 * q] = c0;
-            x[OFF + 4 * q + 1] = c1;
-            x[OFF + 4 * q + 2] = c2;
-            x[OFF + 4 * q + 3] = c3;
-        }
-    }
-};
 
 __device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
 __device__ __forceinline__ bool wave_any(bool v) { return ballot(v) != 0; }
@@ -326,7 +272,7 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
         rep.set_counts(N);
     }
 
-    EventDraw<NQ> dr;
+    EventDraw<NQ, SH> dr;
     dr.k0 = (uint32_t)a.seed;
     dr.k1 = (uint32_t)(a.seed >> 32);
     dr.net_id = a.net_id;

@@ -22,6 +22,7 @@
 #include "bitops.h"
 #include "bwg.h"
 #include "bwg_internal.h"
+#include "event_draw.h"
 
 namespace bwg {
 
@@ -67,7 +68,8 @@ __device__ __forceinline__ int32_t lat_init_count(uint64_t seed, uint32_t net_id
 
 __device__ __forceinline__ uint32_t lat_neighbour(const LatShape &sh, uint32_t s, uint32_t dir)
 {
-    uint32_t x = s % (uint32_t)sh.lx, y = s / (uint32_t)sh.lx;
+    // s / lx by the reciprocal 2^24 / lx, rounded up: exact for s, lx <= 4096
+    uint32_t y = (uint32_t)(((uint64_t)s * sh.inv_lx) >> 24), x = s - y * (uint32_t)sh.lx;
     if (dir == 0)
         x = x + 1 == (uint32_t)sh.lx ? 0 : x + 1;
     else if (dir == 1)
@@ -401,19 +403,6 @@ __device__ __forceinline__ uint32_t less_than_w(const uint32_t (&j)[W], const ui
     return br;
 }
 
-template <int W>
-__device__ __forceinline__ void add_w(uint32_t (&out)[W], const uint32_t (&x)[W],
-                                      const uint32_t (&y)[W])
-{
-    uint32_t c = 0;
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-        const uint32_t s = BWG_OP3(x[q], y[q], c, L_XOR3);
-        c = BWG_OP3(x[q], y[q], c, L_MAJ);
-        out[q] = s;
-    }
-}
-
 template <int P>
 __device__ __forceinline__ void load_site(const uint32_t *p, uint32_t (&l)[P], uint32_t (&d)[P],
                                           uint32_t (&a)[P])
@@ -453,65 +442,251 @@ __device__ __forceinline__ void store_site(uint32_t *p, const uint32_t (&l)[P],
     }
 }
 
-// Threshold planes 0 .. nq-1 of event e for the 32 lanes of word G (the
-// EVENT draws of the well-mixed kernel); planes >= nq are zero.
-template <int BC>
-__device__ __forceinline__ void event_planes(uint32_t (&n)[BC], uint64_t seed, uint32_t net_id,
-                                             uint32_t G, uint64_t e, int nq)
+// ---- a site's reaction with weights known at compile time -------------------
+// Every quantity in exactly the planes its largest value over a site's states
+// (at most T = 2^P - 1 molecules) needs, and no plane that is known to be zero.
+
+constexpr int lat_bits(uint64_t v) { return v ? 1 + lat_bits(v >> 1) : 0; }
+constexpr int lat_ctz(uint64_t v) { return v & 1 ? 0 : 1 + lat_ctz(v >> 1); }
+
+// out (WO planes) = a (WA planes) + b (WB planes), the sum known to fit.
+template <int WO, int WA, int WB>
+__device__ __forceinline__ void add_planes(uint32_t (&out)[WO], const uint32_t (&a)[WA],
+                                           const uint32_t (&b)[WB])
 {
+    constexpr int WMIN = WA < WB ? WA : WB, WMAX = WA < WB ? WB : WA;
+    uint32_t c = 0;
 #pragma unroll
-    for (int k = 0; 4 * k < BC; ++k) {
-        uint32_t o[4] = {0, 0, 0, 0};
-        if (4 * k < nq)
-            philox4x32_10((uint32_t)e,
-                          (DOM_EVENT << 24) | ((uint32_t)k << 16) | ((uint32_t)(e >> 32) & 0xFFFFu),
-                          G, net_id, (uint32_t)seed, (uint32_t)(seed >> 32), o[0], o[1], o[2],
-                          o[3]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (4 * k + j < BC) n[4 * k + j] = (4 * k + j < nq) ? o[j] : 0u;
+    for (int q = 0; q < WO; ++q) {
+        if (q >= WMAX) {
+            out[q] = c;  // the last carry
+            continue;
+        }
+        const uint32_t u = q < WMIN || WA > WB ? a[q < WA ? q : 0] : b[q < WB ? q : 0];
+        const uint32_t v = q < WMIN ? b[q < WB ? q : 0] : c;
+        if (q > 0 && q < WMIN) {
+            out[q] = BWG_OP3(u, v, c, L_XOR3);
+            c = BWG_OP3(u, v, c, L_MAJ);
+        } else {
+            out[q] = u ^ v;
+            c = u & v;
+        }
     }
 }
 
+// x * y of two 4-plane numbers with x + y <= 15: at most 56, six planes.
+__device__ __forceinline__ void mul_6(uint32_t (&p)[6], const uint32_t (&x)[4],
+                                      const uint32_t (&y)[4])
+{
+    constexpr uint32_t L_AND3 = lut(TA & TB & TC);
+    uint32_t t, c;
+    p[0] = x[0] & y[0];
+    t = x[0] & y[1];
+    p[1] = BWG_OP3(x[1], y[0], t, L_ANDXOR);
+    c = BWG_OP3(x[1], y[0], t, L_AND3);
+    uint32_t u = x[2] & y[0];
+    t = x[1] & y[1];
+    p[2] = BWG_OP3(u, t, c, L_XOR3);
+    c = BWG_OP3(u, t, c, L_MAJ);
+    u = x[3] & y[0];
+    t = x[2] & y[1];
+    p[3] = BWG_OP3(u, t, c, L_XOR3);
+    c = BWG_OP3(u, t, c, L_MAJ);
+    p[4] = BWG_OP3(x[3], y[1], c, L_ANDXOR);
+    p[5] = BWG_OP3(x[3], y[1], c, L_AND3);
+    // + x y_2 2^2
+    c = BWG_OP3(x[0], y[2], p[2], L_AND3);
+    p[2] = BWG_OP3(x[0], y[2], p[2], L_ANDXOR);
+    t = x[1] & y[2];
+    u = BWG_OP3(p[3], t, c, L_MAJ);
+    p[3] = BWG_OP3(p[3], t, c, L_XOR3);
+    t = x[2] & y[2];
+    c = BWG_OP3(p[4], t, u, L_MAJ);
+    p[4] = BWG_OP3(p[4], t, u, L_XOR3);
+    t = x[3] & y[2];
+    p[5] = BWG_OP3(p[5], t, c, L_XOR3);
+    // + x y_3 2^3
+    c = BWG_OP3(x[0], y[3], p[3], L_AND3);
+    p[3] = BWG_OP3(x[0], y[3], p[3], L_ANDXOR);
+    t = x[1] & y[3];
+    u = BWG_OP3(p[4], t, c, L_MAJ);
+    p[4] = BWG_OP3(p[4], t, c, L_XOR3);
+    t = x[2] & y[3];
+    p[5] = BWG_OP3(p[5], t, u, L_XOR3);
+}
+
+// acc (W planes, in planes [0, top) so far) +- x << SH.
+template <int W, int P, int SH, bool NEG>
+__device__ __forceinline__ void acc_digit(uint32_t (&acc)[W], const uint32_t (&x)[P])
+{
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = SH; q < W; ++q) {
+        const bool in = q - SH < P;
+        const uint32_t v = in ? x[q - SH < P ? q - SH : 0] : 0u, o = acc[q];
+        if (q == SH) {
+            acc[q] = o ^ v;
+            c = NEG ? ~o & v : o & v;
+        } else if (in) {
+            acc[q] = BWG_OP3(o, v, c, L_XOR3);
+            c = NEG ? BWG_OP3(o, v, c, L_BORROW) : BWG_OP3(o, v, c, L_MAJ);
+        } else {
+            acc[q] = o ^ c;
+            c = NEG ? ~o & c : o & c;
+        }
+    }
+}
+
+// acc = K x over the signed digits of K (no two neighbouring ones), the
+// highest first.
+template <int W, int P, int64_t K, int k = 40>
+__device__ __forceinline__ void times_const(uint32_t (&acc)[W], const uint32_t (&x)[P])
+{
+    constexpr int64_t pos = (3 * K & ~K) >> 1, neg = (K & ~(3 * K)) >> 1;
+    if constexpr (k >= 0) {
+        if constexpr (k < W && ((pos >> k) & 1)) acc_digit<W, P, k, false>(acc, x);
+        if constexpr (k < W && ((neg >> k) & 1)) acc_digit<W, P, k, true>(acc, x);
+        times_const<W, P, K, k - 1>(acc, x);
+    }
+}
+
+// Borrow of n[0 .. WN) - s[0 .. WS) (WS <= WN) from the borrow in.
+template <int WN, int WS>
+__device__ __forceinline__ uint32_t borrow_of(const uint32_t *n, const uint32_t (&s)[WS],
+                                              uint32_t br)
+{
+#pragma unroll
+    for (int q = 0; q < WN; ++q)
+        br = q < WS ? BWG_OP3(n[q], s[q < WS ? q : 0], br, L_BORROW) : ~n[q] & br;
+    return br;
+}
+
+// Widths of the weights c_u, c_a = c_i = 2^F (F planes of S_3 .. S_5 are those
+// of S_2 = 2 U, so the comparisons share one borrow below them).
+template <int P, int64_t CU, int64_t CA, int64_t CI>
+struct LatWidths {
+    static constexpr bool CT = P == 4 && CU > 0 && CA > 0 && CA == CI && (CA & (CA - 1)) == 0;
+    static constexpr int T = (1 << P) - 1;
+    static constexpr int F = CT ? lat_ctz((uint64_t)CA) : 0;
+    static constexpr int UW = CT ? lat_bits((uint64_t)CU * T) : 1;         // U = c_u A
+    static constexpr int64_t most()
+    {
+        int64_t m = 0;
+        for (int64_t a = 0; a <= T; ++a)
+            for (int64_t l = 0; a + l <= T; ++l)
+                for (int64_t d = 0; a + l + d <= T; ++d) {
+                    const int64_t w = 2 * CU * a + CA * (a * l + a * d) + CI * l * d;
+                    m = w > m ? w : m;
+                }
+        return m;
+    }
+    static constexpr int64_t MOST = CT ? most() : 1;
+    static constexpr int SW = lat_bits((uint64_t)MOST);                     // selection planes
+    static constexpr int HU = UW + 1 - F;                                   // 2 U >> F
+    static constexpr int H3 = lat_bits(((uint64_t)(2 * CU * T) >> F) + 56);
+    static constexpr bool SPLIT = CT && HU > 0 && HU <= 6 && UW > 1 && F > 1;
+};
+
+// The event's changers from its threshold planes n (SW planes): lanes of
+// A -> L or A + L -> 2L (mL), A -> D or A + D -> 2D (mD), L + D -> 2A (mI).
+// 240 instructions for c = (246, 246, 2048, 2048, 2048), where forming every
+// S_r in 19 planes and comparing each over all of them took 480.
+template <int64_t CU, int64_t CA, int64_t CI>
+__device__ __forceinline__ void lat_select(const uint32_t *n, const uint32_t (&l)[4],
+                                           const uint32_t (&d)[4], const uint32_t (&x)[4],
+                                           uint32_t &mL, uint32_t &mD, uint32_t &mI)
+{
+    using Wd = LatWidths<4, CU, CA, CI>;
+    constexpr int F = Wd::F, UW = Wd::UW, SW = Wd::SW, HU = Wd::HU, HW = SW - F;
+    uint32_t U[UW];
+#pragma unroll
+    for (int q = 0; q < UW; ++q) U[q] = 0;
+    times_const<UW, 4, CU>(U, x);
+    // S_1 = U and S_2 = 2 U
+    const uint32_t lt1 = borrow_of<SW, UW>(n, U, 0u);
+    uint32_t low = 0;  // borrow of n - 2 U below plane F
+#pragma unroll
+    for (int q = 1; q < F; ++q)
+        low = q - 1 < UW ? BWG_OP3(n[q], U[q - 1 < UW ? q - 1 : 0], low, L_BORROW) : ~n[q] & low;
+    uint32_t h2[HU];
+#pragma unroll
+    for (int q = 0; q < HU; ++q) h2[q] = U[F - 1 + q];
+    const uint32_t lt2 = borrow_of<HW, HU>(n + F, h2, low);
+    // S_r >> F for r = 3, 4, 5 (A L + A D and their sum with the rest of 2 U
+    // stay below 64, with L D below 128: checked by the widths)
+    uint32_t p[6], h3[6], h4[6], h5[HW];
+    static_assert(Wd::H3 <= 6 && HW >= 6, "site weights beyond the planes below");
+    static_assert((Wd::MOST & (Wd::MOST - 1)) != 0, "2^B_r equal to the largest weight");
+    mul_6(p, x, l);
+    add_planes<6, HU, 6>(h3, h2, p);
+    const uint32_t lt3 = borrow_of<HW, 6>(n + F, h3, low);
+    mul_6(p, x, d);
+    add_planes<6, 6, 6>(h4, h3, p);
+    const uint32_t lt4 = borrow_of<HW, 6>(n + F, h4, low);
+    mul_6(p, l, d);
+    if constexpr (HW == 6) {
+        add_planes<6, 6, 6>(h5, h4, p);
+    } else {
+        uint32_t t[7];
+        add_planes<7, 6, 6>(t, h4, p);
+#pragma unroll
+        for (int q = 0; q < HW; ++q) h5[q] = q < 7 ? t[q < 7 ? q : 0] : 0u;
+    }
+    const uint32_t lt5 = borrow_of<HW, HW>(n + F, h5, low);
+    mL = lt1 | (lt3 & ~lt2);
+    mD = (lt2 & ~lt1) | (lt4 & ~lt3);
+    mI = lt5 & ~lt4;
+}
+
 // Reaction component of a site (planes l, d, x already loaded, updated in
-// place) for the lanes in act; returns the lanes whose state changed (the
+// place) for the lanes in act, n the event's threshold planes (4 NQ of them,
+// those from B_r on still drawn); returns the lanes whose state changed (the
 // caller stores the planes if any did).
-template <int P, int BC, int64_t CU, int64_t CA, int64_t CI>
+template <int P, int BC, int NQ, int64_t CU, int64_t CA, int64_t CI>
 __device__ __forceinline__ uint32_t lat_reaction(uint32_t (&l)[P], uint32_t (&d)[P],
-                                                 uint32_t (&x)[P], const LatArgs &a, uint32_t G,
-                                                 uint64_t e, uint32_t act)
+                                                 uint32_t (&x)[P], const LatArgs &a,
+                                                 uint32_t (&n)[4 * NQ], uint32_t act)
 {
     constexpr int WP = 2 * P;
+    using Wd = LatWidths<P, CU, CA, CI>;
     const LatShape &sh = a.sh;
-    uint32_t n[BC];
-    event_planes<BC>(n, a.seed, a.net_id, G, e, sh.B_r);
-
-    // S_1 = cu A, S_2 = 2 cu A, S_3 = S_2 + c_a A L, S_4 = S_3 + c_a A D,
-    // S_5 = S_4 + c_i L D (table order A->L, A->D, A+L->2L, A+D->2D, L+D->2A)
-    uint32_t X[BC];
+    uint32_t mL, mD, mI;
+    if constexpr (Wd::SPLIT) {
+        lat_select<CU, CA, CI>(n, l, d, x, mL, mD, mI);
+    } else {
+        static_assert(BC <= 4 * NQ, "threshold planes");
+        uint32_t t[BC];
 #pragma unroll
-    for (int q = 0; q < BC; ++q) X[q] = 0;
-    add_const_mul<BC, P, CU>(X, x, sh.cu);
-    const uint32_t lt1 = less_than<BC>(n, X);
-    uint32_t S[BC];
-    S[0] = 0;
+        for (int q = 0; q < BC; ++q) t[q] = q < sh.B_r ? n[q] : 0u;
+        // S_1 = cu A, S_2 = 2 cu A, S_3 = S_2 + c_a A L, S_4 = S_3 + c_a A D,
+        // S_5 = S_4 + c_i L D (table order A->L, A->D, A+L->2L, A+D->2D, L+D->2A)
+        uint32_t X[BC];
 #pragma unroll
-    for (int q = 1; q < BC; ++q) S[q] = X[q - 1];
-    const uint32_t lt2 = less_than<BC>(n, S);
-    uint32_t pr[WP];
-    mul_planes<P, WP>(pr, x, l);
-    add_const_mul<BC, WP, CA>(S, pr, sh.ca);
-    const uint32_t lt3 = less_than<BC>(n, S);
-    mul_planes<P, WP>(pr, x, d);
-    add_const_mul<BC, WP, CA>(S, pr, sh.ca);
-    const uint32_t lt4 = less_than<BC>(n, S);
-    mul_planes<P, WP>(pr, l, d);
-    add_const_mul<BC, WP, CI>(S, pr, sh.ci);
-    const uint32_t lt5 = less_than<BC>(n, S);
-
-    const uint32_t mL = (lt1 | (lt3 & ~lt2)) & act;
-    const uint32_t mD = ((lt2 & ~lt1) | (lt4 & ~lt3)) & act;
-    const uint32_t mI = lt5 & ~lt4 & act;
+        for (int q = 0; q < BC; ++q) X[q] = 0;
+        add_const_mul<BC, P, CU>(X, x, sh.cu);
+        const uint32_t lt1 = less_than<BC>(t, X);
+        uint32_t S[BC];
+        S[0] = 0;
+#pragma unroll
+        for (int q = 1; q < BC; ++q) S[q] = X[q - 1];
+        const uint32_t lt2 = less_than<BC>(t, S);
+        uint32_t pr[WP];
+        mul_planes<P, WP>(pr, x, l);
+        add_const_mul<BC, WP, CA>(S, pr, sh.ca);
+        const uint32_t lt3 = less_than<BC>(t, S);
+        mul_planes<P, WP>(pr, x, d);
+        add_const_mul<BC, WP, CA>(S, pr, sh.ca);
+        const uint32_t lt4 = less_than<BC>(t, S);
+        mul_planes<P, WP>(pr, l, d);
+        add_const_mul<BC, WP, CI>(S, pr, sh.ci);
+        const uint32_t lt5 = less_than<BC>(t, S);
+        mL = lt1 | (lt3 & ~lt2);
+        mD = (lt2 & ~lt1) | (lt4 & ~lt3);
+        mI = lt5 & ~lt4;
+    }
+    mL &= act;
+    mD &= act;
+    mI &= act;
     const uint32_t ch = mL | mD | mI;
     if (ch) {
         add_pm1<P>(l, mL, mI);
@@ -529,27 +704,24 @@ __device__ __forceinline__ uint32_t lat_reaction(uint32_t (&l)[P], uint32_t (&d)
 template <int P>
 __device__ __forceinline__ void lat_hop(bool self, uint32_t (&l)[P],
                                         uint32_t (&d)[P], uint32_t (&x)[P], uint32_t (&l2)[P],
-                                        uint32_t (&d2)[P], uint32_t (&x2)[P], const LatArgs &a,
-                                        uint32_t G, uint64_t e, uint32_t act, uint32_t &moved,
+                                        uint32_t (&d2)[P], uint32_t (&x2)[P],
+                                        const uint32_t (&o)[4], uint32_t act, uint32_t &moved,
                                         uint32_t &blocked)
 {
     static_assert(P <= 4, "hop index from one Philox quad");
-    uint32_t o[4];
-    philox4x32_10((uint32_t)e, (DOM_EVENT << 24) | ((uint32_t)(e >> 32) & 0xFFFFu), G, a.net_id,
-                  (uint32_t)a.seed, (uint32_t)(a.seed >> 32), o[0], o[1], o[2], o[3]);
     uint32_t j[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) j[q] = o[q];
     uint32_t al[P], tot[P];
-    add_w<P>(al, x, l);     // site totals are at most T = 2^P - 1: no carry out
-    add_w<P>(tot, al, d);
+    add_planes<P, P, P>(al, x, l);  // site totals are at most T = 2^P - 1: no carry out
+    add_planes<P, P, P>(tot, al, d);
     const uint32_t hA = less_than_w<P>(j, x);
     const uint32_t cAL = less_than_w<P>(j, al);
     const uint32_t any = less_than_w<P>(j, tot) & act;
     const uint32_t sA = hA & act, sL = cAL & ~hA & act, sD = any & ~cAL;
-    uint32_t t2[P], full = ~0u;
-    add_w<P>(t2, x2, l2);
-    add_w<P>(t2, t2, d2);
+    uint32_t t1[P], t2[P], full = ~0u;
+    add_planes<P, P, P>(t1, x2, l2);
+    add_planes<P, P, P>(t2, t1, d2);
 #pragma unroll
     for (int q = 0; q < P; ++q) full &= t2[q];
     const uint32_t mv = any & ~full;
@@ -562,6 +734,21 @@ __device__ __forceinline__ void lat_hop(bool self, uint32_t (&l)[P],
     add_pm1<P>(x2, sA & mv, 0u);
     add_pm1<P>(l2, sL & mv, 0u);
     add_pm1<P>(d2, sD & mv, 0u);
+}
+
+// The 4 NQ threshold planes of event e for the lanes of word G.
+template <int NQ>
+__device__ __forceinline__ void event_draw(const LatArgs &a, uint32_t G, uint64_t e,
+                                           uint32_t (&n)[4 * NQ])
+{
+    EventDraw<NQ> dr;
+    dr.k0 = (uint32_t)a.seed;
+    dr.k1 = (uint32_t)(a.seed >> 32);
+    dr.net_id = a.net_id;
+    dr.G = G;
+    asm volatile("" : "+v"(dr.G));  // not hoisted out of the event loop
+    dr.set_word((uint32_t)(e >> 32) & 0xFFFFu);
+    dr.draw((uint32_t)e, n);
 }
 
 // Lanes of a word that run event e (E_l <= e < Et_l); kept out of line so the
@@ -595,6 +782,18 @@ __device__ __noinline__ uint32_t lanes_at(const uint64_t *sE, const uint64_t *sE
 // 3392 sites, 83 % of a 64 x 64 lattice, but a word's layers hold ~550
 // independent events on average, half of the 1024 threads a CU needs to
 // hide latency: measured slower.)
+//
+// Bound by the latency of a layer: schedule record, then planes, then about
+// 150 (hop) or 430 (reaction) instructions, then the barrier, at one
+// workgroup of 16 waves a CU.  The next event's loads overlap the current
+// event's arithmetic only as long as nothing spills (a scratch load waits in
+// order behind them), hence two register sets that trade places instead of a
+// copied one, the windows in LDS, 32-bit plane offsets and draws whose
+// per-word part is formed again for each event.  A launch of the 64 x 64
+// lattice at 2^16 replicas takes 3102 us (3344 before, with the run-time
+// selection and copied registers; 3435 with 17 spilled registers, 3847 with
+// the records read a further event ahead); a pass of the 21 x 17 one at 1000
+// replicas 1681 us (2042).
 template <int P, int BC, int64_t CU, int64_t CA, int64_t CI, int WS, int BLOCK, int ST>
 __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
 {
@@ -623,27 +822,37 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
     }
     if (tid < 2 * WS) sred[tid / WS][tid % WS] = 0;
     __syncthreads();
-    // window of this thread's word over its pending lanes (E < Et): [lo, hi)
-    // holds every event of the word, [blo, bhi) the events every pending
-    // lane runs; [wlo, whi) the union over the slice
-    uint64_t lo = ~0ull, hi = 0, blo = 0, bhi = ~0ull, wlo = ~0ull, whi = 0;
-    uint32_t pend = 0;
-    for (int l = 0; l < 32; ++l) {
-        const uint64_t e0 = sE[lw][l], e1 = sEt[lw][l];
-        if (e0 < e1) {
-            pend |= 1u << l;
-            lo = min(lo, e0);
-            hi = max(hi, e1);
-            blo = max(blo, e0);
-            bhi = min(bhi, e1);
+    // window of each word over its pending lanes (E < Et): [lo, hi) holds every
+    // event of the word, [blo, bhi) the events every pending lane runs; kept in
+    // LDS, since only the start of a chunk needs them
+    __shared__ uint64_t win[WS][4];
+    __shared__ uint32_t spend[WS];
+    if (tid < WS) {
+        uint64_t lo = ~0ull, hi = 0, blo = 0, bhi = ~0ull;
+        uint32_t p = 0;
+        for (int l = 0; l < 32; ++l) {
+            const uint64_t e0 = sE[tid][l], e1 = sEt[tid][l];
+            if (e0 < e1) {
+                p |= 1u << l;
+                lo = min(lo, e0);
+                hi = max(hi, e1);
+                blo = max(blo, e0);
+                bhi = min(bhi, e1);
+            }
         }
+        win[tid][0] = lo;
+        win[tid][1] = hi;
+        win[tid][2] = blo;
+        win[tid][3] = bhi;
+        spend[tid] = p;
     }
-    for (int k = 0; k < WS * 32; ++k) {
-        const uint64_t e0 = sE[k / 32][k % 32], e1 = sEt[k / 32][k % 32];
-        if (e0 < e1) {
-            wlo = min(wlo, e0);
-            whi = max(whi, e1);
-        }
+    __syncthreads();
+    const uint32_t pend = spend[lw];
+    // the union of the slice's windows
+    uint64_t wlo = ~0ull, whi = 0;
+    for (int k = 0; k < WS; ++k) {
+        wlo = min(wlo, win[k][0]);
+        whi = max(whi, win[k][1]);
     }
     const int S = a.sh.S;
     uint32_t n_real = 0, n_blocked = 0;
@@ -662,21 +871,29 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
     }
     // planes of site st of this thread's word: LDS for staged sites.  The two
     // cases stay separate instructions (LDS and memory loads wait on their own
-    // counters, so the next event's memory loads still overlap this event)
+    // counters, so the next event's memory loads still overlap this event).
+    // A group's planes start at a wave-uniform address, the rest is a 32-bit
+    // offset (4096 sites of 64 words).
+    uint32_t *const gplanes = a.planes + (uint64_t)g * S * LAT_GROUP_WORDS * NP;
+    const uint32_t wofs = (uint32_t)(w % LAT_GROUP_WORDS);
     auto load_at = [&](uint32_t st, uint32_t (&l_)[P], uint32_t (&d_)[P], uint32_t (&x_)[P]) {
         if (ST > 0 && st < nst)
             load_site<P>(reinterpret_cast<const uint32_t *>(&stage[3 * (st * WS + lw)]), l_, d_, x_);
         else
-            load_site<P>(site_planes(a.planes, w, st, S, NP), l_, d_, x_);
+            load_site<P>(gplanes + (st * LAT_GROUP_WORDS + wofs) * NP, l_, d_, x_);
     };
     auto store_at = [&](uint32_t st, const uint32_t (&l_)[P], const uint32_t (&d_)[P],
                         const uint32_t (&x_)[P]) {
         if (ST > 0 && st < nst)
             store_site<P>(reinterpret_cast<uint32_t *>(&stage[3 * (st * WS + lw)]), l_, d_, x_);
         else
-            store_site<P>(site_planes(a.planes, w, st, S, NP), l_, d_, x_);
+            store_site<P>(gplanes + (st * LAT_GROUP_WORDS + wofs) * NP, l_, d_, x_);
     };
     if (runs) {
+        // the draws' per-word part is formed again for every event: kept in
+        // registers it spilled others to scratch, whose loads wait in order
+        // behind the next event's planes
+        constexpr int NQ = (BC + 3) / 4;
         for (uint32_t c = 0; c < a.n_chunks; ++c) {
             const uint32_t *slotp = a.sched + ((uint64_t)g * LAT_NCB + c) * LAT_SLOT;
             const uint32_t *recs = slotp;
@@ -684,62 +901,74 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
             const uint64_t cbase = a.base + (uint64_t)(a.chunk0 + c) * LAT_CH;
             if (cbase >= whi || cbase + LAT_CH <= wlo) continue;
             const uint32_t nl = offs[0];
+            // whether every pending lane of every word runs the whole chunk
+            bool full = true;
+            for (int k = 0; k < WS; ++k)
+                full = full && (win[k][0] > win[k][1] ||
+                                (win[k][2] <= cbase && win[k][3] >= cbase + LAT_CH));
+            full = __builtin_amdgcn_readfirstlane(full);
+            // one event with the planes of its sites
+            struct Fetched {
+                uint32_t rec, s2, act;
+                uint32_t l[P], d[P], x[P], l2[P], d2[P], x2[P];
+            };
+            auto fetch = [&](Fetched &f, uint32_t i) {
+                f.rec = recs[i];
+                const uint32_t off = f.rec >> 16, st = (f.rec >> 3) & 0x1FFFu, kind = f.rec & 7u;
+                f.act = pend;
+                if (!full) {
+                    const uint64_t e = cbase + off;
+                    if (e < win[lw][0] || e >= win[lw][1])
+                        f.act = 0;
+                    else if (e < win[lw][2] || e >= win[lw][3])
+                        f.act = lanes_at(sE[lw], sEt[lw], pend, e);
+                }
+                f.s2 = kind ? lat_neighbour(a.sh, st, kind - 1) : st;
+                if (f.act) {
+                    load_at(st, f.l, f.d, f.x);
+                    if (kind) load_at(f.s2, f.l2, f.d2, f.x2);
+                }
+            };
+            auto apply = [&](Fetched &f) {
+                if (!f.act) return;
+                const uint64_t e = cbase + (f.rec >> 16);
+                const uint32_t st = (f.rec >> 3) & 0x1FFFu;
+                if ((f.rec & 7u) == 0) {
+                    uint32_t n[4 * NQ];
+                    event_draw<NQ>(a, (uint32_t)w, e, n);
+                    const uint32_t ch =
+                        lat_reaction<P, BC, NQ, CU, CA, CI>(f.l, f.d, f.x, a, n, f.act);
+                    if (ch) store_at(st, f.l, f.d, f.x);
+                    n_real += __popc(ch);
+                } else {
+                    uint32_t o[4], mv, bl;
+                    event_draw<1>(a, (uint32_t)w, e, o);
+                    lat_hop<P>(f.s2 == st, f.l, f.d, f.x, f.l2, f.d2, f.x2, o, f.act, mv, bl);
+                    if (mv) {
+                        store_at(st, f.l, f.d, f.x);
+                        store_at(f.s2, f.l2, f.d2, f.x2);
+                    }
+                    n_real += __popc(mv);
+                    n_blocked += __popc(bl);
+                }
+            };
             for (uint32_t L = 0; L < nl; ++L) {
                 const uint32_t end = offs[2 + L];
                 // the planes of this thread's next event of the layer are
-                // loaded while the current one computes: events of a layer
-                // touch disjoint sites, so nothing else writes them meanwhile
+                // loaded while the current one computes (events of a layer
+                // touch disjoint sites, so nothing else writes them
+                // meanwhile), in two sets of registers that trade places
                 uint32_t idx = offs[1 + L] + slot;
-                uint64_t e = 0;
-                uint32_t s = 0, s2 = 0, kind = 0, act = 0;
-                uint32_t l[P], d[P], x[P], l2[P], d2[P], x2[P];
-                auto fetch = [&](uint32_t i) {
-                    const uint32_t rec = recs[i];
-                    e = cbase + (rec >> 16);
-                    act = 0;
-                    if (e >= lo && e < hi)
-                        act = (e >= blo && e < bhi) ? pend : lanes_at(sE[lw], sEt[lw], pend, e);
-                    s = (rec >> 3) & 0x1FFFu;
-                    kind = rec & 7u;
-                    s2 = kind ? lat_neighbour(a.sh, s, kind - 1) : s;
-                    if (act) {
-                        load_at(s, l, d, x);
-                        if (s2 != s) load_at(s2, l2, d2, x2);
-                    }
-                };
-                if (idx < end) fetch(idx);
+                Fetched f0, f1;
+                if (idx < end) fetch(f0, idx);
                 while (idx < end) {
-                    const uint64_t e_c = e;
-                    const uint32_t s_c = s, s2_c = s2, kind_c = kind, act_c = act;
-                    uint32_t lc[P], dc[P], xc[P], l2c[P], d2c[P], x2c[P];
-#pragma unroll
-                    for (int q = 0; q < P; ++q) {
-                        lc[q] = l[q];
-                        dc[q] = d[q];
-                        xc[q] = x[q];
-                        l2c[q] = s2_c == s_c ? l[q] : l2[q];
-                        d2c[q] = s2_c == s_c ? d[q] : d2[q];
-                        x2c[q] = s2_c == s_c ? x[q] : x2[q];
-                    }
                     idx += EV;
-                    if (idx < end) fetch(idx);
-                    if (!act_c) continue;
-                    if (kind_c == 0) {
-                        const uint32_t ch = lat_reaction<P, BC, CU, CA, CI>(lc, dc, xc, a,
-                                                                            (uint32_t)w, e_c, act_c);
-                        if (ch) store_at(s_c, lc, dc, xc);
-                        n_real += __popc(ch);
-                    } else {
-                        uint32_t mv, bl;
-                        lat_hop<P>(s2_c == s_c, lc, dc, xc, l2c, d2c, x2c, a, (uint32_t)w, e_c,
-                                   act_c, mv, bl);
-                        if (mv) {
-                            store_at(s_c, lc, dc, xc);
-                            store_at(s2_c, l2c, d2c, x2c);
-                        }
-                        n_real += __popc(mv);
-                        n_blocked += __popc(bl);
-                    }
+                    if (idx < end) fetch(f1, idx);
+                    apply(f0);
+                    if (idx >= end) break;
+                    idx += EV;
+                    if (idx < end) fetch(f0, idx);
+                    apply(f1);
                 }
                 __syncthreads();
             }

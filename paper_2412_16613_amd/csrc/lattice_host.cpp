@@ -121,6 +121,7 @@ int lat_net_setup(bwg_net *n, const bwg_net_desc *d)
         return fail(BWG_ERANGE, "total component weight beyond 2^56");
     sh.C = (uint64_t)C;
     sh.thresh = (0 - sh.C) % sh.C;
+    sh.inv_lx = ((1u << 24) + (uint32_t)sh.lx - 1) / (uint32_t)sh.lx;
     n->T = (int32_t)T;
     n->lat = true;
     q.B = B;

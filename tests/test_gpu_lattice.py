@@ -72,6 +72,16 @@ def test_fixed_event_count(lx, ly, M, K):
     np.testing.assert_array_equal(blocked, g)
 
 
+@pytest.mark.parametrize("lx,ly", [(4096, 1), (1, 4096), (2048, 2), (1365, 3), (63, 65)])
+def test_long_axes(lx, ly):
+    """Row and column of a site at the ends of the longest axes, where the
+    division by the row length is closest to its error bound."""
+    ens, orc = pair(lattice(lx, ly), 33)
+    ens.step(30000)
+    orc.step(30000)
+    check(ens, orc, "step")
+
+
 @pytest.mark.parametrize("lds_stage", [True, False])
 @pytest.mark.parametrize("M", [16384 + 1000 + 7, 40000 + 5])
 def test_sliced_workgroups_every_replica(M, lds_stage):
