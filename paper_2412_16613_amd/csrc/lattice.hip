@@ -47,12 +47,18 @@ __device__ __forceinline__ uint64_t lat_component(uint64_t seed, uint32_t net_id
 }
 
 // A uniform in {lo..hi} for (replica i, site s): 32-bit Lemire with rejection
-// over the four outputs of successive INIT draws.
+// over the four outputs of successive INIT draws; R = hi - lo + 1, thresh =
+// 2^32 mod R.  Nearly always the first output is taken, so it is formed by
+// itself (the last rounds' other products fall away).
 __device__ __forceinline__ int32_t lat_init_count(uint64_t seed, uint32_t net_id, uint64_t i,
-                                                  uint32_t s, int32_t lo, int32_t hi)
+                                                  uint32_t s, int32_t lo, uint32_t R,
+                                                  uint32_t thresh)
 {
-    const uint32_t R = (uint32_t)(hi - lo + 1);
-    const uint32_t thresh = (0u - R) % R;
+    uint32_t f, u0, u1, u2;
+    philox4x32_10(s, (DOM_INIT << 24) | (1u << 23), (uint32_t)i, net_id, (uint32_t)seed,
+                  (uint32_t)(seed >> 32), f, u0, u1, u2);
+    const uint64_t m0 = (uint64_t)f * R;
+    if (__builtin_expect((uint32_t)m0 >= thresh, 1)) return lo + (int32_t)(m0 >> 32);
     for (uint32_t attempt = 0; attempt < 65536; ++attempt) {
         uint32_t o[4];
         philox4x32_10(s, (DOM_INIT << 24) | (1u << 23) | attempt, (uint32_t)i, net_id,
@@ -130,29 +136,56 @@ __global__ void lat_init_fixed_kernel(uint32_t *planes, uint64_t words, uint64_t
 }
 
 // mode 1: A uniform in {lo..hi} per (replica, site), L = D = 0.  A wave holds
-// 64 replicas (two words) of one site and packs their counts with ballots.
-__global__ void lat_init_uniform_kernel(uint32_t *planes, uint64_t words, uint64_t M, int S, int P,
-                                       int32_t lo, int32_t hi, uint64_t seed, uint32_t net_id,
-                                       uint64_t *E, uint64_t *Et, uint64_t *real,
-                                       uint64_t *blocked)
+// 64 replicas (two words) of one site at a time and packs their counts with
+// ballots; it takes LAT_INIT_SITES sites, so that the products of the first
+// two Philox rounds, which depend on the replica or on the site alone, are
+// formed once or by the scalar unit.  Bound by the draws' multiplications:
+// 509 us for 64 x 64 sites of 2^16 replicas (985 with a site per thread and
+// every output formed).
+constexpr int LAT_INIT_SITES = 8;
+
+__global__ __launch_bounds__(256) void lat_init_uniform_kernel(
+    uint32_t *planes, uint64_t words, uint64_t M, int S, int P, int32_t lo, int32_t hi,
+    uint64_t seed, uint32_t net_id, uint64_t *E, uint64_t *Et, uint64_t *real, uint64_t *blocked)
 {
     // blockDim.x is a multiple of 64; grid.x covers 64 * ceil(words / 2) replicas
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t s = blockIdx.y;
+    const uint32_t s0 = blockIdx.y * LAT_INIT_SITES;
+    const uint32_t s1 = min(s0 + LAT_INIT_SITES, (uint32_t)S);
     const bool ok = i < M;
-    const int32_t a = ok ? lat_init_count(seed, net_id, i, s, lo, hi) : 0;
     const uint64_t w = i >> 5;
     const int lane = threadIdx.x & 63;
-    for (int q = 0; q < P; ++q) {
-        const uint64_t bits = __ballot(ok && ((a >> q) & 1));
-        if ((lane & 31) == 0 && w < words) {
-            uint32_t *p = site_planes(planes, w, s, S, 3 * P);
-            p[q] = 0u;
-            p[P + q] = 0u;
-            p[2 * P + q] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+    const bool stores = (lane & 31) == 0 && w < words;
+    const uint32_t R = (uint32_t)(hi - lo + 1);
+    const uint32_t thresh = (0u - R) % R;
+    for (uint32_t s = s0; s < s1; ++s) {
+        int32_t a = 0;
+        if (ok) a = lat_init_count(seed, net_id, i, s, lo, R, thresh);
+        uint32_t *p = site_planes(planes, w, s, S, 3 * P);
+        if (P == 4) {
+            uint32_t b[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t bits = __ballot((a & (1 << q)) != 0);
+                b[q] = lane & 32 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+            }
+            if (stores) {
+                uint4 *v = reinterpret_cast<uint4 *>(p);
+                v[0] = v[1] = make_uint4(0u, 0u, 0u, 0u);
+                v[2] = make_uint4(b[0], b[1], b[2], b[3]);
+            }
+            continue;
+        }
+        for (int q = 0; q < P; ++q) {
+            const uint64_t bits = __ballot((a >> q) & 1);
+            if (stores) {
+                p[q] = 0u;
+                p[P + q] = 0u;
+                p[2 * P + q] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+            }
         }
     }
-    if (s == 0 && w < words) {
+    if (s0 == 0 && w < words) {
         E[i] = 0;
         Et[i] = 0;
         if ((i & 31) == 0) {
@@ -992,43 +1025,66 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
 
 // ---- readouts --------------------------------------------------------------
 
-// Species totals over sites of every replica: dst[i*3 + x].  A workgroup
-// takes one word (the piece of the launch starts at word w0): thread t reads
-// lane t mod 32 of the word on every LAT_TOT_SPLIT-th site from t / 32, so a
-// half-wave reads one site's planes once for its 32 lanes and the sites of a
-// word are read in parallel; the partial sums meet in LDS.
-constexpr int LAT_TOT_SPLIT = 8;
+// Species totals over sites of every replica: dst[i*3 + x].  A workgroup takes
+// LAT_TOT_WORDS consecutive words (the piece of the launch starts at word w0):
+// thread t adds the planes of word t mod 8 on every LAT_TOT_SUBS-th site to
+// bit-sliced counters, so 32 replicas share an addition and the kernel is bound
+// by reading the planes.  Counters meet over the 8 sites of a wave by shuffles
+// and over the waves in LDS, where each (species, replica) picks out its bits.
+// 97 us for the 402 MB of 64 x 64 sites of 2^16 replicas, 4.1 TB/s (450 with a
+// thread per replica).
+constexpr int LAT_TOT_WORDS = 8, LAT_TOT_SUBS = 128;
+constexpr int LAT_TOT_BLOCK = LAT_TOT_WORDS * LAT_TOT_SUBS;
 
 template <int P>
-__global__ __launch_bounds__(32 * LAT_TOT_SPLIT) void lat_totals_kernel(const uint32_t *planes,
-                                                                        uint64_t M, int S,
-                                                                        int32_t *dst, uint64_t w0)
+__global__ __launch_bounds__(LAT_TOT_BLOCK) void lat_totals_kernel(const uint32_t *planes,
+                                                                   uint64_t M, int S,
+                                                                   int32_t *dst, uint64_t w0)
 {
-    __shared__ int32_t part[LAT_TOT_SPLIT][3][32];
-    const uint64_t w = w0 + blockIdx.x;
-    const uint32_t lane = threadIdx.x & 31, sub = threadIdx.x >> 5;
-    int32_t t[3] = {0, 0, 0};
-    // several sites' loads in flight per thread
-#pragma unroll 4
-    for (int s = (int)sub; s < S; s += LAT_TOT_SPLIT) {
-        uint32_t l[P], d[P], x[P];
-        load_site<P>(site_planes(planes, w, (uint32_t)s, S, 3 * P), l, d, x);
+    // planes of a wave's sum over its 8 threads a word
+    constexpr int PT = P + 8, NW = LAT_TOT_BLOCK / 64;
+    static_assert((int64_t)LAT_MAX_SITES / LAT_TOT_SUBS * 8 * ((1 << P) - 1) < (1 << PT),
+                  "counter planes");
+    __shared__ uint32_t part[NW][3][PT][LAT_TOT_WORDS];
+    const uint32_t t = threadIdx.x, lw = t % LAT_TOT_WORDS, sub = t / LAT_TOT_WORDS;
+    const uint64_t wb = w0 + (uint64_t)blockIdx.x * LAT_TOT_WORDS;
+    uint32_t c[3][PT];
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-            t[0] += (int32_t)((l[q] >> lane) & 1u) << q;
-            t[1] += (int32_t)((d[q] >> lane) & 1u) << q;
-            t[2] += (int32_t)((x[q] >> lane) & 1u) << q;
-        }
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int q = 0; q < PT; ++q) c[k][q] = 0;
+    // several sites' loads in flight per thread
+#pragma unroll 2
+    for (uint32_t s = sub; s < (uint32_t)S; s += LAT_TOT_SUBS) {
+        uint32_t l[P], d[P], x[P];
+        load_site<P>(site_planes(planes, wb + lw, s, S, 3 * P), l, d, x);
+        acc_digit<PT, P, 0, false>(c[0], l);
+        acc_digit<PT, P, 0, false>(c[1], d);
+        acc_digit<PT, P, 0, false>(c[2], x);
     }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) part[sub][k][lane] = t[k];
-    __syncthreads();
-    if (threadIdx.x < 96) {
-        const uint32_t k = threadIdx.x / 32, r = threadIdx.x % 32;
-        int32_t v = 0;
+    for (int o = LAT_TOT_WORDS; o < 64; o *= 2)
 #pragma unroll
-        for (int j = 0; j < LAT_TOT_SPLIT; ++j) v += part[j][k][r];
-        const uint64_t i = 32 * w + r;
+        for (int k = 0; k < 3; ++k) {
+            uint32_t y[PT];
+#pragma unroll
+            for (int q = 0; q < PT; ++q) y[q] = (uint32_t)__shfl_xor((int)c[k][q], o, 64);
+            acc_digit<PT, PT, 0, false>(c[k], y);
+        }
+    if (t % 64 < LAT_TOT_WORDS)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int q = 0; q < PT; ++q) part[t / 64][k][q][lw] = c[k][q];
+    __syncthreads();
+    for (uint32_t o = t; o < 3 * 32 * LAT_TOT_WORDS; o += LAT_TOT_BLOCK) {
+        const uint32_t r = o / 3, k = o % 3;
+        int32_t v = 0;
+        for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int q = 0; q < PT; ++q)
+                v += (int32_t)((part[j][k][q][r / 32] >> (r % 32)) & 1u) << q;
+        const uint64_t i = 32 * wb + r;
         if (i < M) dst[3 * i + k] = v;
     }
 }
@@ -1084,7 +1140,8 @@ hipError_t launch_lat_init(uint32_t *planes, uint64_t words, uint64_t M, int S, 
                            sites_dev, c3[0], c3[1], c3[2], E, Et, real, blocked);
     } else {
         const uint64_t reps = 64 * ((words + 1) / 2);
-        dim3 grid((unsigned)((reps + 255) / 256), (unsigned)S);
+        dim3 grid((unsigned)((reps + 255) / 256),
+                  (unsigned)((S + LAT_INIT_SITES - 1) / LAT_INIT_SITES));
         hipLaunchKernelGGL(lat_init_uniform_kernel, grid, dim3(256), 0, s, planes, words, M, S, P,
                            lo, hi, seed, net_id, E, Et, real, blocked);
     }
@@ -1130,11 +1187,10 @@ hipError_t launch_lat_totals(const uint32_t *planes, uint64_t M, int S, int P, i
                              hipStream_t s)
 {
     if (P != 4) return hipErrorInvalidValue;
-    // one workgroup per word
-    constexpr uint32_t block = 32 * LAT_TOT_SPLIT;
-    return launch_pieces((M + 31) / 32 * block, block, [&](uint64_t i0, dim3 g) {
-        hipLaunchKernelGGL(lat_totals_kernel<4>, g, dim3(block), 0, s, planes, M, S, dst,
-                           i0 / block);
+    const uint64_t n = ((M + 31) / 32 + LAT_TOT_WORDS - 1) / LAT_TOT_WORDS;
+    return launch_pieces(n * LAT_TOT_BLOCK, LAT_TOT_BLOCK, [&](uint64_t i0, dim3 g) {
+        hipLaunchKernelGGL(lat_totals_kernel<4>, g, dim3(LAT_TOT_BLOCK), 0, s, planes, M, S, dst,
+                           i0 / LAT_TOT_BLOCK * LAT_TOT_WORDS);
     });
 }
 

@@ -82,6 +82,20 @@ def test_long_axes(lx, ly):
     check(ens, orc, "step")
 
 
+@pytest.mark.parametrize("lx,ly,M", [(1, 1, 1), (5, 3, 33), (8, 16, 256), (43, 3, 257),
+                                     (64, 64, 2048 + 70)])
+def test_totals_are_the_sums_over_sites(lx, ly, M):
+    """Fewer sites than a workgroup's threads of one word, as many and more;
+    words that fill a workgroup, leave a remainder and cross a group; the
+    uniform initial counts of a site count that is no multiple of eight."""
+    ens, orc = pair(lattice(lx, ly), M)
+    check(ens, orc, "init")
+    ens.step(500)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(ens.read_counts().cpu().numpy(),
+                                  gpu_sites(ens, orc).sum(axis=1))
+
+
 @pytest.mark.parametrize("lds_stage", [True, False])
 @pytest.mark.parametrize("M", [16384 + 1000 + 7, 40000 + 5])
 def test_sliced_workgroups_every_replica(M, lds_stage):
