@@ -196,18 +196,24 @@ __global__ __launch_bounds__(256) void lat_init_uniform_kernel(
 }
 
 // ---- schedule -------------------------------------------------------------------
-// One wave per (group, chunk of LAT_CH events).  Slot layout (uint32):
+// One workgroup per (group, chunk of LAT_CH events).  Slot layout (uint32):
 //   recs[LAT_CH]   events in layer order: (offset in chunk) << 16 | site << 3 | kind
-//   tmp[LAT_CH]    per event: layer << 16 | site << 3 | kind (layer 0: outside)
+//                  (within a layer in any order)
+//   tmp[LAT_CH]    per event: other site << 16 | site << 3 | kind (~0: outside),
+//                  then layer << 16 | site << 3 | kind (0: outside)
 //   offs[0]        number of layers; offs[1 + L] = first event of layer L
 //                  (L = 0 .. layers), so layer L is recs[offs[1+L] .. offs[2+L]).
 // kind 0 is the site's reaction component, 1 + d a hop in direction d.
+//
+// The layers are a serial chain over the chunk's batches of 64 events, walked
+// by one wave; the draws before it and the sort after it are shared by
+// LAT_SCHED_BLOCK threads, and the chain's LDS traffic is one round trip a
+// round (a stamp that grows from round to round needs no clearing between
+// them).  A launch of 32 groups by 32 chunks over 64 x 64 sites takes 114 us
+// (316 with one wave a workgroup, three barriers a round and 56 KB of LDS, of
+// which two workgroups fit a CU).
+constexpr int LAT_SCHED_BLOCK = 256;
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-    for (int o = 32; o; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
     for (int o = 32; o; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
@@ -240,13 +246,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane)
     return v;
 }
 
-__global__ __launch_bounds__(64) void lat_schedule_kernel(LatArgs a)
+__global__ __launch_bounds__(LAT_SCHED_BLOCK) void lat_schedule_kernel(LatArgs a)
 {
-    __shared__ uint16_t last[LAT_MAX_SITES];
-    __shared__ uint32_t first[LAT_MAX_SITES];
-    __shared__ uint32_t hist[LAT_CH];  // two 16-bit counters per word, key = 2 layer + hop
+    constexpr int NW = LAT_SCHED_BLOCK / 64;
+    // the sort's counters take the place of the chain's site tables: two
+    // 16-bit counters per word, key = 2 layer + hop
+    __shared__ uint32_t lds[LAT_CH];
+    static_assert(LAT_MAX_SITES * 3 / 2 <= LAT_CH, "site tables");
+    uint32_t *const hist = lds;
+    uint32_t *const first = lds;
+    uint16_t *const last = reinterpret_cast<uint16_t *>(lds + LAT_MAX_SITES);
+    __shared__ uint64_t wlo[NW], whi[NW];
+    __shared__ uint32_t s_nl;
 
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t ci = blockIdx.x % a.n_chunks;
     const uint32_t g = blockIdx.x / a.n_chunks;
     uint32_t *slot = a.sched + ((uint64_t)g * LAT_NCB + ci) * LAT_SLOT;
@@ -257,7 +270,8 @@ __global__ __launch_bounds__(64) void lat_schedule_kernel(LatArgs a)
     const uint64_t r0 = (uint64_t)g * LAT_GROUP_WORDS * 32;
     const uint64_t r1 = min(a.M, r0 + LAT_GROUP_WORDS * 32);
     uint64_t lo = ~0ull, hi = 0;
-    for (uint64_t i = r0 + lane; i < r1; i += 64) {
+#pragma unroll 4
+    for (uint64_t i = r0 + tid; i < r1; i += LAT_SCHED_BLOCK) {
         const uint64_t e0 = a.E[i], e1 = a.Et[i];
         if (e0 < e1) {
             lo = min(lo, e0);
@@ -266,101 +280,119 @@ __global__ __launch_bounds__(64) void lat_schedule_kernel(LatArgs a)
     }
     lo = wave_min_u64(lo);
     hi = wave_max_u64(hi);
+    if (lane == 0) {
+        wlo[wave] = lo;
+        whi[wave] = hi;
+    }
+    for (int k = tid; k < LAT_MAX_SITES * 3 / 2; k += LAT_SCHED_BLOCK) lds[k] = 0;
+    __syncthreads();
+    for (int k = 0; k < NW; ++k) {
+        lo = min(lo, wlo[k]);
+        hi = max(hi, whi[k]);
+    }
     const uint64_t cbase = a.base + (uint64_t)(a.chunk0 + ci) * LAT_CH;
     const uint64_t clo = max(cbase, lo), chi = min(cbase + LAT_CH, hi);
     if (clo >= chi) {
-        if (lane == 0) offs[0] = 0;
+        if (tid == 0) offs[0] = 0;
         return;
     }
-    for (int k = lane; k < sh.S; k += 64) {
-        last[k] = 0;
-        first[k] = ~0u;
+
+    for (uint32_t off = tid; off < LAT_CH; off += LAT_SCHED_BLOCK) {
+        const uint64_t e = cbase + off;
+        uint32_t v = ~0u;
+        if (e >= clo && e < chi) {
+            const uint64_t comp = lat_component(a.seed, a.net_id, g, e, sh.C, sh.thresh);
+            const uint64_t q = comp / sh.Wsite;
+            const uint64_t r = comp - q * sh.Wsite;
+            const uint32_t s = (uint32_t)q;
+            const uint32_t kind = r < sh.W_R ? 0u : 1u + (uint32_t)((r - sh.W_R) / sh.W_H);
+            v = ((kind ? lat_neighbour(sh, s, kind - 1) : s) << 16) | (s << 3) | kind;
+        }
+        tmp[off] = v;
     }
-    for (int k = lane; k < LAT_CH; k += 64) hist[k] = 0;
     __syncthreads();
 
     // greedy layers: an event's layer is one more than the last layer that
     // touched either of its sites; within a batch of 64 events, a lane is
     // settled in the round where it is the earliest unsettled lane at both
-    // of its sites, so settled lanes of one round touch disjoint sites.
-    uint32_t maxlay = 0;
-    for (uint32_t b = 0; b < LAT_CH; b += 64) {
-        const uint32_t off = b + lane;
-        const uint64_t e = cbase + off;
-        const bool in = e >= clo && e < chi;
-        uint32_t s = 0, s2 = 0, kind = 0;
-        if (in) {
-            const uint64_t comp = lat_component(a.seed, a.net_id, g, e, sh.C, sh.thresh);
-            const uint64_t q = comp / sh.Wsite;
-            const uint64_t r = comp - q * sh.Wsite;
-            s = (uint32_t)q;
-            kind = r < sh.W_R ? 0u : 1u + (uint32_t)((r - sh.W_R) / sh.W_H);
-            s2 = kind ? lat_neighbour(sh, s, kind - 1) : s;
-        }
-        bool pend = in;
-        uint32_t lay = 0;
-        while (__any(pend)) {
-            if (pend) {
-                atomicMin(&first[s], (uint32_t)lane);
-                atomicMin(&first[s2], (uint32_t)lane);
+    // of its sites, so settled lanes of one round touch disjoint sites.  The
+    // sites' entries of first[] hold the round's stamp and 63 - lane of the
+    // earliest lane; a wave's LDS operations keep their order.
+    if (wave == 0) {
+        uint32_t maxlay = 0, stamp = 0, next = tmp[lane];
+        for (uint32_t b = 0; b < LAT_CH; b += 64) {
+            const uint32_t v = next;
+            if (b + 64 < LAT_CH) next = tmp[b + 64 + lane];
+            const bool in = v != ~0u;
+            const uint32_t s = (v >> 3) & 0x1FFFu, s2 = v >> 16;
+            bool pend = in;
+            uint32_t lay = 0;
+            while (__any(pend)) {
+                stamp += 64;
+                const uint32_t key = stamp | (63u - (uint32_t)lane);
+                if (pend) {
+                    atomicMax(&first[s], key);
+                    atomicMax(&first[s2], key);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (pend) {
+                    const uint32_t f1 = first[s], f2 = first[s2], l1 = last[s], l2 = last[s2];
+                    if (f1 == key && f2 == key) {
+                        lay = 1u + max(l1, l2);
+                        last[s] = (uint16_t)lay;
+                        last[s2] = (uint16_t)lay;
+                        pend = false;
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
-            __syncthreads();
-            bool settled = false;
-            if (pend) settled = first[s] == (uint32_t)lane && first[s2] == (uint32_t)lane;
-            if (settled) {
-                lay = 1u + max((uint32_t)last[s], (uint32_t)last[s2]);
-                last[s] = (uint16_t)lay;
-                last[s2] = (uint16_t)lay;
-            }
-            __syncthreads();
-            if (pend) {
-                first[s] = ~0u;
-                first[s2] = ~0u;
-            }
-            __syncthreads();
-            pend = pend && !settled;
-        }
-        if (in) {
-            const uint32_t key = 2 * (lay - 1) + (kind != 0);
-            atomicAdd(&hist[key >> 1], 1u << (16 * (key & 1)));
             maxlay = max(maxlay, lay);
-            tmp[off] = (lay << 16) | (s << 3) | kind;
-        } else {
-            tmp[off] = 0;
+            tmp[b + lane] = in ? (lay << 16) | (v & 0xFFFFu) : 0u;
         }
+        const uint32_t nl = wave_max_u32(maxlay);
+        if (lane == 0) s_nl = nl;
     }
-    const uint32_t nl = wave_max_u32(maxlay);
     __syncthreads();
+    const uint32_t nl = s_nl;
 
-    // exclusive prefix over keys 0 .. 2 nl - 1, written back as cursors
-    uint32_t run = 0;
-    for (uint32_t kb = 0; kb < 2 * nl; kb += 64) {
-        const uint32_t k = kb + lane;
-        const uint32_t cnt = k < 2 * nl ? (hist[k >> 1] >> (16 * (k & 1))) & 0xFFFFu : 0u;
-        const uint32_t incl = wave_incl_scan(cnt, lane);
-        const uint32_t excl = run + incl - cnt;
-        const uint32_t odd = __shfl_down((int)excl, 1, 64);
-        __syncthreads();
-        if (k < 2 * nl && (k & 1) == 0) {
-            hist[k >> 1] = excl | (odd << 16);
-            offs[1 + (k >> 1)] = excl;
-        }
-        run += __shfl((int)incl, 63, 64);
-        __syncthreads();
-    }
-    if (lane == 0) {
-        offs[0] = nl;
-        offs[1 + nl] = run;
+    // sort by key: count, exclusive prefix over keys 0 .. 2 nl - 1, written
+    // back as cursors, then place
+    for (uint32_t k = tid; k < nl; k += LAT_SCHED_BLOCK) hist[k] = 0;
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t off = tid; off < LAT_CH; off += LAT_SCHED_BLOCK) {
+        const uint32_t t = tmp[off], lay = t >> 16;
+        if (lay) atomicAdd(&hist[lay - 1], (t & 7u) != 0 ? 0x10000u : 1u);
     }
     __syncthreads();
-    for (uint32_t b = 0; b < LAT_CH; b += 64) {
-        const uint32_t off = b + lane;
-        const uint32_t t = tmp[off];
-        const uint32_t lay = t >> 16;
+    if (wave == 0) {
+        uint32_t run = 0;
+        for (uint32_t kb = 0; kb < nl; kb += 64) {
+            const uint32_t k = kb + lane;
+            const uint32_t h = k < nl ? hist[k] : 0u;
+            const uint32_t cnt = (h & 0xFFFFu) + (h >> 16);
+            const uint32_t incl = wave_incl_scan(cnt, lane);
+            const uint32_t excl = run + incl - cnt;
+            if (k < nl) {
+                hist[k] = excl | ((excl + (h & 0xFFFFu)) << 16);
+                offs[1 + k] = excl;
+            }
+            run += __shfl((int)incl, 63, 64);
+        }
+        if (lane == 0) {
+            offs[0] = nl;
+            offs[1 + nl] = run;
+        }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (uint32_t off = tid; off < LAT_CH; off += LAT_SCHED_BLOCK) {
+        const uint32_t t = tmp[off], lay = t >> 16;
         if (lay) {
-            const uint32_t key = 2 * (lay - 1) + ((t & 7u) != 0);
-            const uint32_t sh16 = 16 * (key & 1);
-            const uint32_t old = atomicAdd(&hist[key >> 1], 1u << sh16);
+            const uint32_t sh16 = (t & 7u) != 0 ? 16 : 0;
+            const uint32_t old = atomicAdd(&hist[lay - 1], 1u << sh16);
             recs[(old >> sh16) & 0xFFFFu] = (off << 16) | (t & 0xFFFFu);
         }
     }
@@ -1150,7 +1182,8 @@ hipError_t launch_lat_init(uint32_t *planes, uint64_t words, uint64_t M, int S, 
 
 hipError_t launch_lat_schedule(const LatArgs &a, uint32_t n_groups, hipStream_t s)
 {
-    hipLaunchKernelGGL(lat_schedule_kernel, dim3(n_groups * a.n_chunks), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(lat_schedule_kernel, dim3(n_groups * a.n_chunks),
+                       dim3(LAT_SCHED_BLOCK), 0, s, a);
     return hipGetLastError();
 }
 
