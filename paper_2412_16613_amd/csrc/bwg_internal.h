@@ -208,6 +208,14 @@ hipError_t launch_batch_epilogue(const BatchBudget *bb, int n_ens, hipStream_t s
 constexpr int LAT_GROUP_WORDS = 64;
 constexpr int LAT_CH = 8192;
 constexpr int LAT_NCB = 32;
+// Sites up to which one workgroup holds a word's sites in LDS, beside a chunk's
+// schedule: what fits for the weights known at compile time (44 x 44 sites,
+// 1000 replicas, 32768 events: 347 us against 416 in memory; 21 x 17: 444
+// against 866), and for run-time weights, whose selection is long enough to
+// want the memory kernel's threads, where that overtakes (21 x 17: 1335 against
+// 1927; 32 x 32: 961 against 887).
+constexpr int LAT_WORD_SITES = 1984;
+constexpr int LAT_WORD_SITES_RT = 832;
 constexpr int LAT_SLOT = 3 * LAT_CH + 64;   // uint32 per (group, chunk) slot
 constexpr int LAT_MAX_SITES = 4096;
 

@@ -201,8 +201,9 @@ __global__ __launch_bounds__(256) void lat_init_uniform_kernel(
 //                  (within a layer in any order)
 //   tmp[LAT_CH]    per event: other site << 16 | site << 3 | kind (~0: outside),
 //                  then layer << 16 | site << 3 | kind (0: outside)
-//   offs[0]        number of layers; offs[1 + L] = first event of layer L
-//                  (L = 0 .. layers), so layer L is recs[offs[1+L] .. offs[2+L]).
+//   offs[0]        number of layers; the low half of offs[1 + L] is the first
+//                  event of layer L (L = 0 .. layers), so layer L is
+//                  recs[offs[1+L] .. offs[2+L]); the high half its first hop.
 // kind 0 is the site's reaction component, 1 + d a hop in direction d.
 //
 // The layers are a serial chain over the chunk's batches of 64 events, walked
@@ -377,7 +378,7 @@ __global__ __launch_bounds__(LAT_SCHED_BLOCK) void lat_schedule_kernel(LatArgs a
             const uint32_t excl = run + incl - cnt;
             if (k < nl) {
                 hist[k] = excl | ((excl + (h & 0xFFFFu)) << 16);
-                offs[1 + k] = excl;
+                offs[1 + k] = hist[k];
             }
             run += __shfl((int)incl, 63, 64);
         }
@@ -1018,12 +1019,12 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
                 }
             };
             for (uint32_t L = 0; L < nl; ++L) {
-                const uint32_t end = offs[2 + L];
+                const uint32_t end = offs[2 + L] & 0xFFFFu;
                 // the planes of this thread's next event of the layer are
                 // loaded while the current one computes (events of a layer
                 // touch disjoint sites, so nothing else writes them
                 // meanwhile), in two sets of registers that trade places
-                uint32_t idx = offs[1 + L] + slot;
+                uint32_t idx = (offs[1 + L] & 0xFFFFu) + slot;
                 Fetched f0, f1;
                 if (idx < end) fetch(f0, idx);
                 while (idx < end) {
@@ -1052,6 +1053,180 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
     if (tid < WS && w < words) {
         a.real[w] += sred[0][tid];
         a.blocked[w] += sred[1][tid];
+    }
+}
+
+// One workgroup per word, all of the word's sites (S <= ST) in LDS: for
+// ensembles of fewer words than fill the chip with 4-word slices, where a
+// layer of a small lattice holds fewer events than a workgroup has threads and
+// its latency is all that counts.  A chunk's schedule is copied to LDS as
+// well.  The two halves of the workgroup take the layers in turn: while one
+// half reads planes, selects and writes them back, the other draws the
+// thresholds of the next layer's events, which depend on nothing but the
+// record.  In a half, the first waves take a layer's reactions and the others
+// its hops, so that no wave runs both paths.  512 threads: with 1024 a layer's
+// barrier costs more than the further events in flight give (793 us instead of
+// 664).  Bound by the instructions of one wave, selection on one side and draws
+// on the other, with 40 % of the issue slots used: 599 us for 60000 events of
+// 1000 replicas on 21 x 17 sites, 549 layers (1401 in the kernel above).
+template <int P, int BC, int64_t CU, int64_t CA, int64_t CI, int BLOCK, int ST>
+__global__ __launch_bounds__(BLOCK, 1) void lat_word_kernel(LatArgs a)
+{
+    static_assert(P == 4, "staging holds 12 planes per site");
+    constexpr int NP = 3 * P, NQ = (BC + 3) / 4, HALF = BLOCK / 2, HW = HALF / 64;
+    const uint64_t w = (uint64_t)a.g0 * LAT_GROUP_WORDS + blockIdx.x;
+    const uint32_t g = (uint32_t)(w / LAT_GROUP_WORDS);
+    if (w >= (a.M + 31) / 32 || g >= a.g0 + a.ng) return;
+    const uint32_t tid = threadIdx.x;
+    const int S = a.sh.S;
+    __shared__ uint4 stage[3 * ST];
+    __shared__ uint4 recs4[LAT_CH / 4], offs[LAT_CH / 4 + 1];
+    const uint32_t *const recs = reinterpret_cast<const uint32_t *>(recs4);
+    const uint32_t *const bounds = reinterpret_cast<const uint32_t *>(offs) + 1;
+    __shared__ uint4 window[8];
+    __shared__ uint32_t sred[2];
+
+    // the windows of the word's pending lanes (E < Et): [lo, hi) holds every
+    // event, [blo, bhi) the events every pending lane runs
+    const uint64_t r = 32 * w + (tid & 31);
+    const uint64_t e0 = r < a.M ? a.E[r] : 0, e1 = r < a.M ? a.Et[r] : 0;
+    const uint32_t pend = (uint32_t)__ballot(e0 < e1);
+    const uint64_t lo = wave_min_u64(e0 < e1 ? e0 : ~0ull), hi = wave_max_u64(e0 < e1 ? e1 : 0);
+    const uint64_t blo = wave_max_u64(e0 < e1 ? e0 : 0), bhi = wave_min_u64(e0 < e1 ? e1 : ~0ull);
+    if (tid < 2) sred[tid] = 0;
+    // the launch's events of this word: [lo, hi) within its chunks
+    const uint64_t c_lo = a.base + (uint64_t)a.chunk0 * LAT_CH;
+    const uint64_t c_hi = c_lo + (uint64_t)a.n_chunks * LAT_CH;
+    if (hi <= lo || lo >= c_hi || hi <= c_lo) return;
+
+    for (uint32_t k = tid; k < 3u * S; k += BLOCK)
+        stage[k] = reinterpret_cast<const uint4 *>(site_planes(a.planes, w, k / 3, S, NP))[k % 3];
+    uint32_t n_real = 0, n_blocked = 0;
+    // the second half numbers its waves backwards: waves go to the four SIMDs
+    // in turn, and so one half's selections meet the other half's hops there,
+    // not its reactions' draws
+    const uint32_t half = tid / HALF;
+    const uint32_t ht = half ? (tid % HALF) ^ (HALF - 64) : tid;
+    // waves of a half that take reactions, by their share of the events
+    const uint32_t rw = min(
+        max((uint32_t)((float)HW * (float)a.sh.W_R / (float)a.sh.Wsite + 0.5f), 1u),
+        (uint32_t)HW - 1);
+    const bool hops = __builtin_amdgcn_readfirstlane(ht >= 64 * rw);
+    const uint32_t first = hops ? ht - 64 * rw : ht;
+    const uint32_t stride = hops ? HALF - 64 * rw : 64 * rw;
+
+    for (uint32_t c = 0; c < a.n_chunks; ++c) {
+        const uint64_t cbase = a.base + (uint64_t)(a.chunk0 + c) * LAT_CH;
+        if (cbase >= hi || cbase + LAT_CH <= lo) continue;
+        const uint32_t *slotp = a.sched + ((uint64_t)g * LAT_NCB + c) * LAT_SLOT;
+        const uint32_t nl = slotp[2 * LAT_CH];
+        if (nl == 0) continue;
+        const bool full = blo <= cbase && bhi >= cbase + LAT_CH;
+        // the whole slot of records, so that no load waits for their number
+        static_assert(LAT_CH % (4 * BLOCK) == 0 && LAT_SLOT % 4 == 0, "copies of 16 bytes");
+        uint4 t[LAT_CH / (4 * BLOCK)];
+#pragma unroll
+        for (int j = 0; j < LAT_CH / (4 * BLOCK); ++j)
+            t[j] = reinterpret_cast<const uint4 *>(slotp)[tid + j * BLOCK];
+        // each lane's events of the chunk: the first and their number
+        if (!full && tid < 32) {
+            const uint64_t b = min(max(e0, cbase), cbase + LAT_CH);
+            const uint64_t n = max(min(e1, cbase + LAT_CH), b) - b;
+            reinterpret_cast<uint32_t *>(window)[tid] =
+                e0 < e1 ? (uint32_t)(b - cbase) | ((uint32_t)n << 16) : 0u;
+        }
+        for (uint32_t k = tid; k <= (nl + 1) / 4; k += BLOCK)
+            offs[k] = reinterpret_cast<const uint4 *>(slotp + 2 * LAT_CH)[k];
+#pragma unroll
+        for (int j = 0; j < LAT_CH / (4 * BLOCK); ++j) recs4[tid + j * BLOCK] = t[j];
+        __syncthreads();
+
+        uint32_t idx = 0, end = 0, rec = 0, act = 0, n[4 * NQ];
+        // the drawn planes of this thread's event idx
+        auto draw = [&]() {
+            act = 0;
+            if (idx >= end) return;
+            rec = recs[idx];
+            const uint32_t off = rec >> 16;
+            const uint64_t e = cbase + off;
+            if (full) {
+                act = pend;
+            } else {
+                for (int k = 0; k < 8; ++k) {
+                    const uint4 v = window[k];
+                    const uint32_t m = (uint32_t)(off - (v.x & 0xFFFFu) < v.x >> 16) |
+                                       (uint32_t)(off - (v.y & 0xFFFFu) < v.y >> 16) << 1 |
+                                       (uint32_t)(off - (v.z & 0xFFFFu) < v.z >> 16) << 2 |
+                                       (uint32_t)(off - (v.w & 0xFFFFu) < v.w >> 16) << 3;
+                    act |= m << (4 * k);
+                }
+            }
+            if (!act) return;
+            if (hops) {
+                uint32_t o[4];
+                event_draw<1>(a, (uint32_t)w, e, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) n[q] = o[q];
+            } else {
+                event_draw<NQ>(a, (uint32_t)w, e, n);
+            }
+        };
+        auto prepare = [&](uint32_t L) {
+            idx = end = 0;
+            if (L < nl) {
+                const uint32_t o0 = bounds[L];
+                idx = (hops ? o0 >> 16 : o0 & 0xFFFFu) + first;
+                end = hops ? bounds[L + 1] & 0xFFFFu : o0 >> 16;
+            }
+            draw();
+        };
+        auto apply = [&]() {
+            if (!act) return;
+            const uint32_t st = (rec >> 3) & 0x1FFFu;
+            uint32_t *p = reinterpret_cast<uint32_t *>(&stage[3 * st]);
+            uint32_t l[P], d[P], x[P];
+            load_site<P>(p, l, d, x);
+            if (!hops) {
+                const uint32_t ch = lat_reaction<P, BC, NQ, CU, CA, CI>(l, d, x, a, n, act);
+                if (ch) store_site<P>(p, l, d, x);
+                n_real += __popc(ch);
+            } else {
+                const uint32_t s2 = lat_neighbour(a.sh, st, (rec & 7u) - 1);
+                uint32_t *p2 = reinterpret_cast<uint32_t *>(&stage[3 * s2]);
+                uint32_t l2[P], d2[P], x2[P], mv, bl;
+                load_site<P>(p2, l2, d2, x2);
+                const uint32_t o[4] = {n[0], n[1], n[2], n[3]};
+                lat_hop<P>(s2 == st, l, d, x, l2, d2, x2, o, act, mv, bl);
+                if (mv) {
+                    store_site<P>(p, l, d, x);
+                    store_site<P>(p2, l2, d2, x2);
+                }
+                n_real += __popc(mv);
+                n_blocked += __popc(bl);
+            }
+        };
+        if (half == 0) prepare(0);
+        for (uint32_t L = 0; L < nl; ++L) {
+            if ((L & 1) == half) {
+                apply();
+                for (idx += stride; idx < end; idx += stride) {
+                    draw();
+                    apply();
+                }
+            } else {
+                prepare(L + 1);
+            }
+            __syncthreads();
+        }
+    }
+    if (n_real) atomicAdd(&sred[0], n_real);
+    if (n_blocked) atomicAdd(&sred[1], n_blocked);
+    __syncthreads();
+    for (uint32_t k = tid; k < 3u * S; k += BLOCK)
+        reinterpret_cast<uint4 *>(site_planes(a.planes, w, k / 3, S, NP))[k % 3] = stage[k];
+    if (tid == 0) {
+        a.real[w] += sred[0];
+        a.blocked[w] += sred[1];
     }
 }
 
@@ -1191,21 +1366,30 @@ hipError_t launch_lat_schedule(const LatArgs &a, uint32_t n_groups, hipStream_t 
 // capacity, the weights of A -> L / A -> D, A + L -> 2L / A + D -> 2D and
 // L + D -> 2A (-1: taken at run time), words per slice, threads per
 // workgroup (512 for the run-time weights, which need more registers) and
-// sites staged in LDS (0: none).
+// (site, word) pairs staged in LDS (0: none; with one word per slice, the
+// lattices that lat_word_kernel takes).
 #define BWG_LAT_VARIANTS(X)                                                                   \
     X(0, 4, 19, 246, 2048, 2048, 4, 1024, 0) X(1, 4, 19, 246, 2048, 2048, 1, 1024, 0)          \
     X(2, 4, 19, -1, -1, -1, 4, 512, 0) X(3, 4, 19, -1, -1, -1, 1, 512, 0)                      \
     X(4, 4, 24, -1, -1, -1, 4, 512, 0) X(5, 4, 24, -1, -1, -1, 1, 512, 0)                      \
-    X(6, 4, 19, 246, 2048, 2048, 4, 1024, 4 * BWG_LAT_STAGE_SITES)
+    X(6, 4, 19, 246, 2048, 2048, 4, 1024, 4 * BWG_LAT_STAGE_SITES)                             \
+    X(7, 4, 19, 246, 2048, 2048, 1, 512, LAT_WORD_SITES)                                   \
+    X(8, 4, 19, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT)                                     \
+    X(9, 4, 24, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT)
 
 // grid: the slices of the band's groups, rounded up to a multiple of the 8 XCDs
 #define BWG_LAT_LAUNCH(ID, P_, BC_, CU_, CA_, CI_, WS_, BL_, ST_)                             \
     static hipError_t lat_launch_##ID(const LatArgs &a, uint64_t words, hipStream_t s)       \
     {                                                                                         \
-        (void)words;                                                                          \
         const uint64_t nwg = (uint64_t)a.ng * (LAT_GROUP_WORDS / WS_);                        \
-        hipLaunchKernelGGL((lat_event_kernel<P_, BC_, CU_, CA_, CI_, WS_, BL_, ST_>),         \
-                           dim3((unsigned)(8 * ((nwg + 7) / 8))), dim3(BL_), 0, s, a);        \
+        if constexpr (WS_ == 1 && ST_ > 0) {                                                  \
+            const uint64_t left = words - (uint64_t)a.g0 * LAT_GROUP_WORDS;                   \
+            hipLaunchKernelGGL((lat_word_kernel<P_, BC_, CU_, CA_, CI_, BL_, ST_>),           \
+                               dim3((unsigned)(left < nwg ? left : nwg)), dim3(BL_), 0, s, a); \
+        } else {                                                                              \
+            hipLaunchKernelGGL((lat_event_kernel<P_, BC_, CU_, CA_, CI_, WS_, BL_, ST_>),     \
+                               dim3((unsigned)(8 * ((nwg + 7) / 8))), dim3(BL_), 0, s, a);    \
+        }                                                                                     \
         return hipGetLastError();                                                             \
     }
 BWG_LAT_VARIANTS(BWG_LAT_LAUNCH)

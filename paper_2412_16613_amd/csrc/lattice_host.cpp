@@ -136,7 +136,7 @@ int lat_net_setup(bwg_net *n, const bwg_net_desc *d)
     return BWG_OK;
 }
 
-// Words per workgroup slice: 8 once there are enough slices to fill the
+// Words per workgroup slice: 4 once there are enough slices to fill the
 // chip (coalesced site records), else one word per workgroup.
 static int lat_slice_words(uint64_t M)
 {
@@ -160,8 +160,8 @@ static uint32_t lat_band_groups(const bwg_net *n, int ws, uint64_t groups)
 }
 
 // The event kernel of a lattice for the slice width lat_slice_words picks:
-// the LDS-staged one where one exists and staging is asked for, else the
-// memory one; compile-time weights before run-time ones, then the fewest
+// the LDS-staged one where one exists (with one word per slice it holds every
+// site or is not taken) and staging is asked for, else the memory one; compile-time weights before run-time ones, then the fewest
 // threshold planes.
 static const LatVariant *pick_lat_variant(const bwg_net *n, uint64_t M, bool stage)
 {
@@ -174,6 +174,7 @@ static const LatVariant *pick_lat_variant(const bwg_net *n, uint64_t M, bool sta
         const int ws = lat_slice_words(M);
         if ((v.stage > 0) != (pass == 0)) continue;
         if (v.P != sh.P || v.bc < sh.B_r + 1 || v.ws != ws) continue;
+        if (v.ws == 1 && v.stage > 0 && sh.S > v.stage) continue;
         if (v.cu >= 0 && ((uint64_t)v.cu != sh.cu || (uint64_t)v.ca != sh.ca ||
                           (uint64_t)v.ci != sh.ci))
             continue;

@@ -250,3 +250,34 @@ def test_lds_staged_kernel_equals_memory_kernel(lx, ly, kw, M, t):
         del e
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("lx,ly,kw", [
+    (62, 32, {}),                                              # 1984 sites: all in LDS
+    (397, 5, {}),                                              # 1985: memory kernel
+    (52, 16, dict(k0=0.03, k1=0.2, k2=0.05, hop=0.37)),        # 832, run-time weights
+    (49, 17, dict(k0=0.03, k1=0.2, k2=0.05, hop=0.37)),        # 833: memory kernel
+    (11, 7, dict(hop=0.0)),                                    # reactions only
+    (11, 7, dict(k0=0.0, k1=0.0, k2=0.0)),                     # hops do the work
+    (1, 1, {}),                                                # every event a layer
+])
+def test_one_word_kernel_equals_memory_kernel(lx, ly, kw):
+    """Ensembles below 512 words with every site in LDS and with none: a last
+    word of one lane, a horizon whose lanes end within a chunk, two advances
+    (windows that begin in different chunks)."""
+    net = bwg.Network(lattice(lx, ly, **kw))
+    M = 2048 + 64 + 1
+    t = 12000 / net.lattice()["Lambda"]
+    got = []
+    for stage in (True, False):
+        ens = bwg.Ensemble(net, M, seed=4, net_id=9, lds_stage=stage)
+        ens.init(UNIFORM)
+        ens.advance(t)
+        ens.advance(2.5 * t)
+        torch.cuda.synchronize()
+        ev, real = ens.read_events()
+        got.append((ens.read_sites(0, M).cpu().numpy(), ev.cpu().numpy(),
+                    real.cpu().numpy(), ens.read_blocked().cpu().numpy(), ens.read_counts().cpu().numpy()))
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+    assert (got[0][1] > 0).all()
