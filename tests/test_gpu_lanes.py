@@ -128,6 +128,35 @@ def test_event_indices_cross_a_high_bit(torch, start):
     np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
 
 
+@pytest.mark.parametrize("net", [frank_network(32), frank_network(61, k0=0.02)],
+                         ids=["precompiled", "compiled"])
+def test_word_events_cross_a_high_bit(torch, net):
+    """The same for the word kernel of large ensembles, against the lanes
+    loop: lanes that reach the crossing at different events of a launch, some
+    of which do not reach it."""
+    M = 32 * 32768 + 45
+    n = bwg.Network(net)
+    got = []
+    for engine in ("bitwise", "lanes"):
+        e = bwg.Ensemble(n, M, seed=8, net_id=1, engine=engine)
+        e.init_fixed((0, 0, net["n_tot"]))
+        e.advance(0.2)
+        blob = bytearray(e.save())
+        h = np.frombuffer(blob, dtype=np.uint64, count=32)
+        for k in range(int(h[11])):
+            if int(h[12 + 3 * k]) in (3, 4):
+                v = np.frombuffer(blob, dtype=np.uint64, count=int(h[14 + 3 * k]) // 8,
+                                  offset=int(h[13 + 3 * k]))
+                v[:M] += np.uint64((1 << 32) - 200)
+        e.restore(bytes(blob))
+        e.step(180)
+        e.step(300)
+        got.append((e.read_counts().cpu().numpy(), e.read_events()[0].cpu().numpy()))
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    assert (got[0][1].astype(np.uint64) >= 1 << 32).all()
+
+
 # ---- which loop a bit-sliced ensemble runs --------------------------------------
 
 @pytest.mark.parametrize("net,init", [
