@@ -23,55 +23,37 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# VALU issue slots per word-event (32 replica-events) that the bit-sliced method needs, in
-# the form the well-mixed kernel computes it (word_event_slots).  One slot is one 32-bit VALU
-# instruction per lane; v_mad_u64_u32 issues at the same rate as v_bitop3_b32 (--valu-ref).
+# VALU issue slots: one slot is one 32-bit VALU instruction per lane; v_mad_u64_u32 issues at
+# the same rate as v_bitop3_b32 (--valu-ref).
 PHILOX_SLOTS = 40           # 20 32x32->64 multiply-adds + 20 three-input xors per call
 
 
-def _bitlen(v):
-    return int(v).bit_length()
-
-
-def _signed_width(lo, hi):
-    return max(2, _bitlen(max(hi, -lo - 1)) + 1)
-
-
-def word_event_slots(q, n_tot):
-    """Slots per word-event of the well-mixed Frank event at exact register
-    widths (the molecule count known): RNG, the five cumulative comparisons
-    (borrow chains, the two that feed later ones keep their difference),
-    the changer masks, three masked +-1/+2 ripple updates of the counts, the
-    pair counts P_AL, Q_A = N_A (N_tot - N_A), P_LD (masked change formed
-    over its exact width, then a sign-extended ripple add) and U = c_u N_A."""
-    b, B, N = q["b"], q["B"], n_tot
-    BS = B + (1 if q["max_total"] == (1 << B) else 0)
-    c = q["c"]
-    cu, fa, fi = c[0], _bitlen(c[2]) - 1, _bitlen(c[4]) - 1
-    fmin = min(fa, fi)
-    UW = max(1, _bitlen(cu * N))
-    WP = max(2, _bitlen((N // 2) * (N - N // 2)))
-    wd_al = _signed_width(-N + 1, 2 * N - 4)
-    wd_qa = _signed_width(-2 * N + 4, 2 * N - 4)
-    wd_ld = _signed_width(-N, N - 1)
-    rng = ((B + 3) // 4) * PHILOX_SLOTS
-    select = (UW + -(-(BS - UW - 1) // 2) + 1) + (fmin - 1) + 2 * (BS - fmin) \
-        + (BS - fa) + 2 * (BS - fa) + (BS - fi)
-    masks = 10
-    counts = 3 * (2 * b - 1)
-    products = (5 * wd_al + 2 * WP - 1) + (4 * wd_qa + 2 * WP - 1) + (4 * wd_ld + 2 * WP - 1)
-    unimolecular = 2 * UW - 1
-    return rng + select + masks + counts + products + unimolecular
-
-
-def lanes_event_slots(q, real_fraction):
+def lanes_event_slots(q, real_fraction, drawn_fraction):
     """Slots per word-event of the lanes loop (one replica per lane, 64
-    word-events to a wave's window): the draws with the Philox calls' shared
-    rounds, the 8 x 8 bit transpositions of whole octets of planes, the test
-    of every replica's threshold byte (two instructions), and one application
-    (selection, count change, new weights) per real event."""
+    word-events to a wave's window), the mean over all events of the chain:
+    the draws with the Philox calls' shared rounds, the 8 x 8 bit
+    transpositions of whole octets of planes and the test of every replica's
+    threshold byte (two instructions) for the events that are drawn, and one
+    application (selection, count change, new weights) per real event."""
     nq = (q["B"] + 3) // 4
-    return 5 + 32 * nq + 48 * ((nq + 1) // 2) + 64 + 33 * 32 * real_fraction
+    return (5 + 32 * nq + 48 * ((nq + 1) // 2) + 64) * drawn_fraction + 33 * 32 * real_fraction
+
+
+def drawn_fraction(ens, init, t_end, torch, slices=50):
+    """Share of the events that the lanes loop draws: a wave (64 replicas)
+    stops once all its replicas have reached a state that no event leaves (one
+    enantiomer, no A).  From an untimed run of the same ensemble cut into
+    slices of the horizon."""
+    ens.init(init)
+    n = 0.0
+    for k in range(slices):
+        c = ens.read_counts()
+        live = (c[:, 2] != 0) | ((c[:, 0] != 0) & (c[:, 1] != 0))
+        pad = -live.numel() % 64
+        live = torch.nn.functional.pad(live, (0, pad)).view(-1, 64)
+        n += float(live.any(dim=1).double().mean())
+        ens.advance(t_end * (k + 1) / slices)
+    return n / slices
 
 
 # 32-bit VALU lane-operations/s: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz (a wave64
@@ -85,22 +67,21 @@ HBM_PEAK = 8.0e12               # bytes/s, MI355X HBM3E
 # (the factors of a 1 GiB copy), valid only for the sources they were taken on:
 # kernel -> (sha1 prefix of its sources, sources, bytes per launch, summary file).
 CSRC = os.path.join(ROOT, "paper_2412_16613_amd", "csrc")
+_LANES = ("effab601ec91", ("bitops.h", "event_draw.h", "lanes_device.h", "lanes_kernel.hip",
+                           "wm_device.h"))
+_LATTICE = ("a978bfbb7d7a", ("bitops.h", "bwg_internal.h", "event_draw.h", "lattice.hip"))
 MEASURED_TRAFFIC = {
-    "wm_pc_kernel": ("56dc664d5d4c", ("bitops.h", "wm_device.h", "wm_event_body.inc",
-                                      "wm_kernel.hip"),
-                     (2 * 10822 + 12672) * 1024, "profiles/wm_pc_kernel_frank1024_2p20.md"),
-    "lat_event_kernel": ("ed3743083ea0", ("bitops.h", "bwg_internal.h", "lattice.hip"),
-                         (2 * 5477457 + 11890680) * 1024,
-                         "profiles/lat_event_kernel_lattice64x64_2p16.md"),
+    "wm_lanes_kernel": _LANES + ((2 * 16980 + 12672) * 1024,
+                                 "profiles/wm_lanes_kernel_frank1024_2p20.md"),
+    "lat_event_kernel": _LATTICE + ((2 * 5829760 + 12900400) * 1024,
+                                    "profiles/lat_event_kernel_lattice64x64_2p16.md"),
 }
 
 
 # VALU wave instructions per launch (rocprofv3 SQ_INSTS_VALU), valid for the same sources:
 # kernel -> (sha1 prefix, sources, instructions per launch, summary file).
 MEASURED_VALU = {
-    "wm_pc_kernel": ("56dc664d5d4c", ("bitops.h", "wm_device.h", "wm_event_body.inc",
-                                      "wm_kernel.hip"),
-                     20831937027, "profiles/wm_pc_kernel_frank1024_2p20.md"),
+    "wm_lanes_kernel": _LANES + (9270160000, "profiles/wm_lanes_kernel_frank1024_2p20.md"),
 }
 
 
@@ -280,7 +261,8 @@ def main():
     value = events_per_step * args.steps / (r["ms"] / 1e3)
     adv_avg_ms = sum(r["adv_ms"]) / len(r["adv_ms"])
     word_events = events_per_step / 32.0
-    slots = lanes_event_slots(q, r["real"] / events_per_step)
+    drawn = drawn_fraction(make(args.engine)[0], c["init"], t_end, torch)
+    slots = lanes_event_slots(q, r["real"] / events_per_step, drawn)
     # per event-kernel launch: its share of the step's word-events over its
     # duration (HIP events around each launch, on the launch stream)
     launches_per_step = r["kt_n"] / args.steps
@@ -314,7 +296,7 @@ def main():
                      "traffic_unit": "B/launch",
                      "kernel": kernel, "kernel_ms": launch_ms,
                      "launches_per_step": launches_per_step, "advance_ms": adv_avg_ms,
-                     "slots_per_word_event": slots,
+                     "slots_per_word_event": slots, "drawn_fraction": drawn,
                      "valu_insts_per_launch": measured_valu(kernel) if whole else None,
                      "issued_frac": (measured_valu(kernel) * 64 / (launch_ms / 1e3) /
                                      VALU_PEAK if whole and measured_valu(kernel) else None)},

@@ -19,15 +19,20 @@
 //              count change, new weights.  Where the total weight has passed
 //              the bound, the rest of the window is compared again.
 //
-// Bound by VALU issue: on the N_tot = 1024 workload (2^20 replicas, 23 planes)
-// a wave issues 675 instructions per 64 word-events -- 197 for the draws, 144
-// for the transposition, 64 per comparison of the window and 36 per round of
-// the last step (5 rounds: the busiest of 64 replicas) -- against the
-// bit-sliced word's 800, and unlike that word's one long chain they fill the
-// chip: one instruction per 4.2 cycles and SIMD.  29.0 ms for the workload with
-// every event drawn, where drawing, transposing and testing all 32 thresholds
-// in order took 75.8 ms; 5.7 ms against 11.9 for 2^17 replicas, 4.9 against
-// 6.2 for 16523 replicas of 4 10^4 events of which 42 % are real.
+// Bound by VALU issue on large ensembles: on the N_tot = 1024 workload (2^20
+// replicas, 23 planes) a wave issues about 670 instructions per 64 word-events
+// -- 197 for the draws, 144 for the transposition, 64 per comparison of the
+// window and 34 per round of the last step (5 rounds: the busiest of 64
+// replicas) -- against the bit-sliced word's 800, and unlike that word's one
+// long chain they fill the chip: one instruction per 4.2 cycles and SIMD.  29 ms
+// for the workload with every event drawn, where drawing, transposing and
+// testing all 32 thresholds in order took 75.8 ms; 15.2 ms now that waves whose
+// replicas have all ended stop.  Bound by a round's chain of dependent
+// instructions, about 7 cycles each, where a SIMD holds a wave or none: 3.6 ms
+// against 11.9 for 2^17 replicas, 4.2 against 6.2 for 16523 replicas of 4 10^4
+// events of which 42 % are real.  (Measured there and not kept: a second wave
+// that draws a window ahead, 4.2 -> 5.3 ms; a candidate's bytes read a full
+// round ahead, 4.6 to 4.8 ms; A in a register of its own, 4.3 ms.)
 #pragma once
 
 #include "event_draw.h"
