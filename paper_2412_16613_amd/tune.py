@@ -15,13 +15,14 @@ what any other configuration gives.
 Why lanes: a batch finishes when its longest word chain does.  A bit-sliced
 word runs its 32 replicas' events one after another at ~750-1200 wave
 instructions per event (one lane per word), while a lanes item draws the
-thresholds of 32 events at once, transposes them in registers and then runs
-each event in ~50 instructions for 64 replicas (one replica per lane): about
-twice the work per replica-event of the bit-sliced word on compile-time
-weights, but chains an order of magnitude shorter.  The candidates move the k
-longest chains (events per replica x cost per event) to lanes, k from 0 to
-every member; each is timed on a tenth of the horizons (both the longest
-chain and the total work scale with it).
+thresholds of 32 events at once, transposes them in registers and spends
+instructions on the events that can change a state only: ~10 per event for 64
+replicas where most are null, ~40 where half are not.  Members small enough run
+the lanes loop under the bit-sliced engine as well, so the lanes axis matters
+for the large ones.  The candidates move the k longest chains (events per
+replica x cost per event) to lanes, k from 0 to every member; each is timed on
+a tenth of the horizons (both the longest chain and the total work scale with
+it).
 """
 
 import hashlib
