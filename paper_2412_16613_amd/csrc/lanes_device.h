@@ -29,10 +29,10 @@
 // testing all 32 thresholds in order took 75.8 ms; 15.2 ms now that waves whose
 // replicas have all ended stop.  Bound by a round's chain of dependent
 // instructions, about 7 cycles each, where a SIMD holds a wave or none: 3.6 ms
-// against 11.9 for 2^17 replicas, 4.2 against 6.2 for 16523 replicas of 4 10^4
-// events of which 42 % are real.  (Measured there and not kept: a second wave
-// that draws a window ahead, 4.2 -> 5.3 ms; a candidate's bytes read a full
-// round ahead, 4.6 to 4.8 ms; A in a register of its own, 4.3 ms.)
+// against 11.9 for 2^17 replicas, 4.1 against 6.2 for 16523 replicas of 4 10^4
+// events of which 42 % are real.  (Measured there and not kept: a candidate's
+// bytes read a full round ahead, 4.6 to 4.8 ms; A in a register of its own, 4.3
+// ms.)
 #pragma once
 
 #include "event_draw.h"
@@ -265,8 +265,14 @@ __device__ __forceinline__ void pack_counts(const WmArgs &a, uint64_t w, int l, 
 // wave take every loop together (words past the end and words without
 // pending events with empty masks), so the loops are the wave's own and cost
 // no lane masking.
-template <int NQ, class Replica>
-__device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *sq)
+//
+// PAIR: two waves of one workgroup take the same two words; the one that
+// draws is a window ahead of the one that keeps the replicas, each in another
+// of two buffers (2 HALF words apart).  `ended` is a word of LDS, zero at the
+// start.
+template <int NQ, class Replica, bool PAIR = false>
+__device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *sq,
+                                         bool draws = false, volatile uint32_t *ended = nullptr)
 {
     constexpr int NO = LanesRow<NQ>::NO, SH = LanesRow<NQ>::SH, ROW = LanesRow<NQ>::WORDS;
     const int l = threadIdx.x & 31;
@@ -276,7 +282,7 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
     Replica rep(a);
     {
         uint32_t N[Replica::S] = {};
-        if (valid) unpack_counts(a, w, l, N);
+        if (valid && !draws) unpack_counts(a, w, l, N);
         rep.set_counts(N);
     }
 
@@ -289,7 +295,7 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
     const uint32_t m1 = last > 1 ? ~0u : 0u, m2 = last > 2 ? ~0u : 0u, m3 = last > 3 ? ~0u : 0u;
     // this replica's place in a row: byte l / 8 of word l mod 8 of each octet
     const uint32_t *word = sq + (l & 7);
-    const uint8_t *top = reinterpret_cast<const uint8_t *>(word + 8 * (NO - 1)) + (l >> 3);
+    const uint32_t top_at = 32 * (NO - 1) + (l >> 3);
     const uint32_t sel = (uint32_t)(l >> 3);
     const uint32_t sel2 = 0x0C0C0400u + sel * 0x0101u, sel3 = 0x0C040100u + (sel << 16);
     const uint32_t sel4 = 0x04020100u + (sel << 24);
@@ -321,35 +327,28 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
         const int32_t most = (int32_t)(sp0 > sp1 ? sp0 : sp1);
         dr.set_word((uint32_t)(base >> 32) & 0xFFFFu);
         const uint32_t e_lo = (uint32_t)base + (uint32_t)l;
-        for (int32_t k = 0; k < most; k += 32) {
-            // a state of total weight zero (one enantiomer and no A) is left by
-            // no event: nothing to draw once all replicas of the wave have
-            // reached one (N_tot = 1024, t = 100: 29.0 -> 15.2 ms)
-            done = !wave_any(rep.total() != 0);
-            if (done) break;
-            {
-                uint32_t x[32];
-                dr.draw(e_lo + (uint32_t)k, x);
-                x[8 * NO - 3] &= m1;
-                x[8 * NO - 2] &= m2;
-                x[8 * NO - 1] &= m3;
+        // this thread's event k + l of the window at k
+        auto draw = [&](int32_t k, uint32_t *rows) {
+            uint32_t x[32];
+            dr.draw(e_lo + (uint32_t)k, x);
+            x[8 * NO - 3] &= m1;
+            x[8 * NO - 2] &= m2;
+            x[8 * NO - 1] &= m3;
 #pragma unroll
-                for (int o = 0; o < NO; ++o) {
-                    if (o == 0 && SH)
-                        transpose8<true>(x);
-                    else
-                        transpose8<false>(x + 8 * o);
-                }
-                uint4 *row = reinterpret_cast<uint4 *>(sq + ROW * l);
-#pragma unroll
-                for (int c = 0; c < 2 * NO; ++c)
-                    row[c] = make_uint4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+            for (int o = 0; o < NO; ++o) {
+                if (o == 0 && SH)
+                    transpose8<true>(x);
+                else
+                    transpose8<false>(x + 8 * o);
             }
-            // the half's LDS operations run in program order: the reads
-            // below see every lane's stores, and the next window's stores
-            // follow them
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            uint4 *row = reinterpret_cast<uint4 *>(rows + ROW * l);
+#pragma unroll
+            for (int c = 0; c < 2 * NO; ++c)
+                row[c] = make_uint4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
+        };
+        // the window's events of this thread's replica, from the rows at word
+        auto take = [&](int32_t k) {
+            const uint8_t *top = reinterpret_cast<const uint8_t *>(word) + top_at;
             // this replica's events of the window
             uint32_t ends = ~0u, rem = ~0u;
             if (wave_any(to - k < 32 || from > k)) {
@@ -398,11 +397,50 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
                           ? ~((2u << (31 - __builtin_clz(taken))) - 1u) & ends
                           : 0u;
             } while (wave_any(rem != 0));
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+        };
+        if constexpr (PAIR) {
+            if (draws) {
+                if (most > 0) draw(0, sq);
+                __syncthreads();
+                for (int32_t k = 0; k < most && !done; k += 32) {
+                    const uint32_t to_buf = k & 32 ? 0 : 2 * LanesRow<NQ>::HALF;
+                    if (k + 32 < most) draw(k + 32, sq + to_buf);
+                    __syncthreads();
+                    done = *ended;
+                }
+            } else {
+                __syncthreads();
+                for (int32_t k = 0; k < most && !done; k += 32) {
+                    word = sq + (k & 32 ? 2 * LanesRow<NQ>::HALF : 0) + (l & 7);
+                    done = !wave_any(rep.total() != 0);
+                    if (done)
+                        *ended = 1;
+                    else
+                        take(k);
+                    __syncthreads();
+                }
+            }
+        } else {
+            for (int32_t k = 0; k < most; k += 32) {
+                // a state of total weight zero (one enantiomer and no A) is
+                // left by no event: nothing to draw once all replicas of the
+                // wave have reached one (N_tot = 1024, t = 100: 29.0 -> 15.2 ms)
+                done = !wave_any(rep.total() != 0);
+                if (done) break;
+                draw(k, sq);
+                // the half's LDS operations run in program order: the reads
+                // see every lane's stores, and the next window's stores
+                // follow them
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                take(k);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
         }
         base = base < stop ? stop : base;
     }
+    if (draws) return;
     uint32_t N[Replica::S];
     rep.get_counts(N);
     pack_counts(a, valid ? w : ~0ull, l, hv, v, N, hv ? real1 : real0);

@@ -75,6 +75,25 @@ def test_every_width_of_large_weights(torch, B, n_tot, cu, ca, ci):
           [("step", 500)])
 
 
+# planes on both sides of the rule's quads; the cases above run in pairs of waves
+@pytest.mark.parametrize("words", [511, 512, 513, 2048, 2049])
+@pytest.mark.parametrize("n_tot,cu,ca,ci", [(6, 1, 1, 1), (200, 50, 4, 4), (1000, 100, 4, 4),
+                                            (1000, 1 << 19, 8192, 8192)],
+                         ids=["few", "B17", "B21", "B32"])
+def test_one_wave_and_pairs_of_waves(torch, n_tot, cu, ca, ci, words):
+    """Windows that end within a launch, replicas that end early and words of
+    one half wave only, on both sides of the sizes where a second wave draws."""
+    net = exact_network(n_tot, cu, ca, ci)
+    check(torch, net, 32 * words - 31, ("fixed", (0, 0, n_tot)),
+          [("step", 33), ("advance", 60 / bwg.Network(net).quantized()["Lambda"]), ("step", 100)])
+
+
+@pytest.mark.parametrize("n_tot", [5, 40])
+def test_pairs_of_waves_that_end_early(torch, n_tot):
+    check(torch, frank_network(n_tot, k0=0.3), 64 * 40 + 7, ("fixed", (0, 0, n_tot)),
+          [("step", 40 * n_tot), ("step", 3000)])
+
+
 @pytest.mark.parametrize("cu,ca,ci", [(7, 0, 0), (0, 4, 0), (0, 0, 2), (5, 8, 0), (70000, 0, 64)])
 def test_absent_reactions(torch, cu, ca, ci):
     net = exact_network(90, cu, ca, ci)
