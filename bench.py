@@ -67,11 +67,11 @@ HBM_PEAK = 8.0e12               # bytes/s, MI355X HBM3E
 # (the factors of a 1 GiB copy), valid only for the sources they were taken on:
 # kernel -> (sha1 prefix of its sources, sources, bytes per launch, summary file).
 CSRC = os.path.join(ROOT, "paper_2412_16613_amd", "csrc")
-_LANES = ("effab601ec91", ("bitops.h", "event_draw.h", "lanes_device.h", "lanes_kernel.hip",
+_LANES = ("54962d56c23a", ("bitops.h", "event_draw.h", "lanes_device.h", "lanes_kernel.hip",
                            "wm_device.h"))
 _LATTICE = ("a978bfbb7d7a", ("bitops.h", "bwg_internal.h", "event_draw.h", "lattice.hip"))
 MEASURED_TRAFFIC = {
-    "wm_lanes_kernel": _LANES + ((2 * 16980 + 12672) * 1024,
+    "wm_lanes_kernel": _LANES + ((2 * 16982 + 12672) * 1024,
                                  "profiles/wm_lanes_kernel_frank1024_2p20.md"),
     "lat_event_kernel": _LATTICE + ((2 * 5829760 + 12900400) * 1024,
                                     "profiles/lat_event_kernel_lattice64x64_2p16.md"),
@@ -81,7 +81,7 @@ MEASURED_TRAFFIC = {
 # VALU wave instructions per launch (rocprofv3 SQ_INSTS_VALU), valid for the same sources:
 # kernel -> (sha1 prefix, sources, instructions per launch, summary file).
 MEASURED_VALU = {
-    "wm_lanes_kernel": _LANES + (9270160000, "profiles/wm_lanes_kernel_frank1024_2p20.md"),
+    "wm_lanes_kernel": _LANES + (9270110000, "profiles/wm_lanes_kernel_frank1024_2p20.md"),
 }
 
 
