@@ -262,10 +262,13 @@ __global__ void first_passage_kernel(const uint32_t *planes, const int32_t *coun
     if ((d < 0 ? -d : d) >= threshold) first[i] = k;
 }
 
-__global__ void copy_u64_kernel(const uint64_t *src, uint64_t *dst, uint64_t n, uint64_t i0)
+// Two copies in one launch (n2 <= n; n2 = 0: one).
+__global__ void copy_u64_kernel(const uint64_t *src, uint64_t *dst, uint64_t n,
+                                const uint64_t *src2, uint64_t *dst2, uint64_t n2, uint64_t i0)
 {
     const uint64_t i = i0 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) dst[i] = src[i];
+    if (i < n2) dst2[i] = src2[i];
 }
 
 // dst[slot] = sum(src[0..n)) with one block (used by stats, not hot).
@@ -403,10 +406,12 @@ hipError_t launch_first_passage(const uint32_t *planes, const int32_t *counts, i
     });
 }
 
-hipError_t launch_copy_u64(const uint64_t *src, uint64_t *dst, uint64_t n, hipStream_t s)
+hipError_t launch_copy_u64(const uint64_t *src, uint64_t *dst, uint64_t n, hipStream_t s,
+                           const uint64_t *src2, uint64_t *dst2, uint64_t n2)
 {
+    if (n2 > n) return hipErrorInvalidValue;
     return launch_pieces(n, 256, [&](uint64_t i0, dim3 g) {
-        hipLaunchKernelGGL(copy_u64_kernel, g, dim3(256), 0, s, src, dst, n, i0);
+        hipLaunchKernelGGL(copy_u64_kernel, g, dim3(256), 0, s, src, dst, n, src2, dst2, n2, i0);
     });
 }
 

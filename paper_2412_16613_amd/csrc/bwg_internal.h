@@ -310,7 +310,9 @@ hipError_t launch_gather_counts(const uint32_t *planes, const int32_t *counts, i
 hipError_t launch_first_passage(const uint32_t *planes, const int32_t *counts, int nb,
                                 uint64_t wp, uint64_t M, int32_t threshold, uint32_t k,
                                 uint32_t *first, hipStream_t s);
-hipError_t launch_copy_u64(const uint64_t *src, uint64_t *dst, uint64_t n, hipStream_t s);
+hipError_t launch_copy_u64(const uint64_t *src, uint64_t *dst, uint64_t n, hipStream_t s,
+                           const uint64_t *src2 = nullptr, uint64_t *dst2 = nullptr,
+                           uint64_t n2 = 0);
 hipError_t launch_sum_u64(const uint64_t *src, uint64_t n, uint64_t *dst2, int slot,
                           hipStream_t s);
 

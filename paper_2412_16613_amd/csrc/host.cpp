@@ -1398,16 +1398,14 @@ extern "C" int bwg_ensemble_read_events(bwg_ens *e, uint64_t *dev_events, uint64
 {
     if (!e) return fail(BWG_EINVAL, "null ensemble");
     hipStream_t s = (hipStream_t)stream;
-    if (dev_events && e->zs)
-        HIP_TRY(launch_fill_u64(dev_events, e->M, e->zE, s));
-    else if (dev_events)
-        HIP_TRY(launch_copy_u64(e->E, dev_events, e->M, s));
-    if (dev_real) {
-        if (e->engine != BWG_ENGINE_PLAIN)
-            HIP_TRY(launch_copy_u64(e->real, dev_real, (e->M + 31) / 32, s));
-        else
-            HIP_TRY(launch_copy_u64(e->real, dev_real, e->M, s));
+    const uint64_t n_real =
+        !dev_real ? 0 : (e->engine != BWG_ENGINE_PLAIN ? (e->M + 31) / 32 : e->M);
+    if (dev_events && !e->zs) {
+        HIP_TRY(launch_copy_u64(e->E, dev_events, e->M, s, e->real, dev_real, n_real));
+        return BWG_OK;
     }
+    if (dev_events) HIP_TRY(launch_fill_u64(dev_events, e->M, e->zE, s));
+    if (dev_real) HIP_TRY(launch_copy_u64(e->real, dev_real, n_real, s));
     return BWG_OK;
 }
 
