@@ -268,8 +268,11 @@ __device__ __forceinline__ void pack_counts(const WmArgs &a, uint64_t w, int l, 
 //
 // PAIR: two waves of one workgroup take the same two words; the one that
 // draws is a window ahead of the one that keeps the replicas, each in another
-// of two buffers (2 HALF words apart).  `ended` is a word of LDS, zero at the
-// start.
+// of two buffers (2 HALF words apart).  `ended` is two words of LDS: for every
+// window the replicas' wave writes whether the chain ended there into the word
+// of the window's parity before the barrier that closes it, and the drawing
+// wave reads it after that barrier.  That word is written again only after the
+// next barrier, so both waves leave at the same one.
 template <int NQ, class Replica, bool PAIR = false>
 __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *sq,
                                          bool draws = false, volatile uint32_t *ended = nullptr)
@@ -406,17 +409,15 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
                     const uint32_t to_buf = k & 32 ? 0 : 2 * LanesRow<NQ>::HALF;
                     if (k + 32 < most) draw(k + 32, sq + to_buf);
                     __syncthreads();
-                    done = *ended;
+                    done = __builtin_amdgcn_readfirstlane(ended[(k >> 5) & 1]) != 0;
                 }
             } else {
                 __syncthreads();
                 for (int32_t k = 0; k < most && !done; k += 32) {
                     word = sq + (k & 32 ? 2 * LanesRow<NQ>::HALF : 0) + (l & 7);
                     done = !wave_any(rep.total() != 0);
-                    if (done)
-                        *ended = 1;
-                    else
-                        take(k);
+                    ended[(k >> 5) & 1] = done;
+                    if (!done) take(k);
                     __syncthreads();
                 }
             }

@@ -23,12 +23,11 @@ template <int NQ, bool FULL>
 __global__ __launch_bounds__(128) void wm_lanes_pair_kernel(WmArgs a)
 {
     __shared__ __align__(16) uint32_t sq[4][LanesRow<NQ>::HALF];
-    __shared__ uint32_t ended;
+    __shared__ uint32_t ended[2];
     const uint32_t half = (threadIdx.x >> 5) & 1;
     const bool draws = __builtin_amdgcn_readfirstlane(threadIdx.x >= 64);
-    if (threadIdx.x == 0) ended = 0;
     wm_lanes<NQ, FrankReplica<FULL>, true>(a, 2 * (uint64_t)blockIdx.x + half, sq[half], draws,
-                                           &ended);
+                                           ended);
 }
 
 __global__ __launch_bounds__(256) void wm_lanes_shared_kernel(WmArgs a, uint64_t w0)

@@ -94,6 +94,15 @@ def test_pairs_of_waves_that_end_early(torch, n_tot):
           [("step", 40 * n_tot), ("step", 3000)])
 
 
+@pytest.mark.parametrize("steps", [31, 32, 33, 64, 65, 96, 97, 160, 1000])
+def test_pairs_of_waves_leave_at_the_same_window(torch, steps):
+    """One pair of waves whose chain ends in the first, an even or an odd, the
+    last or no window of a launch, by the seed; a second launch finds it ended."""
+    for seed in range(8):
+        check(torch, paper_network(3), 64, ("multinomial",), [("step", steps), ("step", steps)],
+              seed=seed)
+
+
 @pytest.mark.parametrize("cu,ca,ci", [(7, 0, 0), (0, 4, 0), (0, 0, 2), (5, 8, 0), (70000, 0, 64)])
 def test_absent_reactions(torch, cu, ca, ci):
     net = exact_network(90, cu, ca, ci)
