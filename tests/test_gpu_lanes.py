@@ -130,7 +130,7 @@ def test_totals_that_outgrow_the_bound(torch):
     check(torch, net, 40, ("fixed", (200, 0, 0)), [("step", 100)])
 
 
-@pytest.mark.parametrize("start", [(1 << 32) - 200, (1 << 34) - 31])
+@pytest.mark.parametrize("start", [(1 << 26) - 77, (1 << 32) - 200, (1 << 34) - 31])
 def test_event_indices_cross_a_high_bit(torch, start):
     net = frank_network(40, k0=0.05)
     M = 77
@@ -310,6 +310,21 @@ def test_general_networks_on_both_kernels(torch, name, word_bits):
     want = np.zeros((M + 31) // 32, np.uint64)
     np.add.at(want, np.arange(M) // 32, o.real.astype(np.uint64))
     np.testing.assert_array_equal(real.cpu().numpy().astype(np.uint64), want)
+
+
+def test_real_events_of_one_launch_past_32_bits(torch):
+    """L and D turn into each other, two molecules, total weight 2 = 2^B: every
+    event of every replica is real, 2^32 and some of the one word in a launch."""
+    net = table(3, [((1, 0, 0), (0, 1, 0)), ((0, 1, 0), (1, 0, 0))], [1, 1], 2)
+    assert bwg.Network(net).quantized()["B"] == 1
+    n = (1 << 27) + 5
+    e = bwg.Ensemble(bwg.Network(net), 32, seed=3)
+    e.init_fixed((1, 1, 0)).step(n)
+    ev, real = e.read_events()
+    assert (ev == n).all() and real.tolist() == [32 * n]
+    assert e.stats()["real_total"] == 32 * n
+    c = e.read_counts()
+    assert (c[:, 0] + c[:, 1] == 2).all() and (c >= 0).all()
 
 
 # ---- states that nothing leaves -----------------------------------------------------
