@@ -439,8 +439,8 @@ static std::string jit_source_lanes(const bwg_net &n)
         if (n.open)
             for (int x = 0; x < S; ++x)
                 if (dv(j, x) > 0)
-                    blocked += (blocked.empty() ? "" : " || ") + ("n[" + std::to_string(x) + "] > ") +
-                               std::to_string(n.n_tot - dv(j, x)) + "u";
+                    blocked += (blocked.empty() ? "" : " || ") + ("n[" + std::to_string(x) + "] + ") +
+                               std::to_string(dv(j, x)) + "u > " + std::to_string(n.n_tot) + "u";
         if (!blocked.empty()) o << "            const bool blocked = " << blocked << ";\n";
         for (int k = 0; k < regs; ++k) {
             int32_t d = dv(j, 2 * k);

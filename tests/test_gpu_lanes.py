@@ -287,6 +287,10 @@ GENERAL = {
     # caps that block firings most of the time
     "capped4": (random_wide_network(6, 4, 9, 10, open_net=True), ("fixed", (9, 8, 9, 7))),
     "capped7": (random_wide_network(12, 7, 30, 16, open_net=True), ("fixed", (29,) * 7)),
+    # a cap of one: gains of two that no state has room for, beside one that fits
+    "cap1": (table(2, [((1, 0), (1, 2)), ((1, 0), (1, 1)), ((0, 1), (0, 0))], [3, 1, 2], 1,
+                   open_net=True), ("fixed", (1, 0))),
+    "cap1alone": (table(1, [((1,), (3,))], [1], 1, open_net=True), ("fixed", (1,))),
 }
 
 
