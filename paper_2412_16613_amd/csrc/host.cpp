@@ -1289,7 +1289,8 @@ extern "C" int bwg_ensemble_histogram(bwg_ens *e, int32_t n_bins, uint64_t *dst,
 // registers (a launch per point, its first-passage and gather kernels and the
 // budgets took 0.17 ms a point at 2^22 replicas, ten events of which are
 // 0.01).  A point of more events than the table holds runs in launches of its
-// own before the recording one, which then has none left for it.
+// own before the recording one, which then has none left for it.  A point that
+// is refused ends the recording after the points before it have run.
 static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, const WmArgs &what,
                          hipStream_t s)
 {
@@ -1298,15 +1299,16 @@ static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, co
     const uint64_t cap = (e->table_cap - ends) * 2;
     uint64_t *dev_end = e->table + (e->table_cap - ends);
     uint32_t k = 0;
-    while (k < n_points) {
+    int refused = BWG_OK;
+    while (k < n_points && !refused) {
         std::vector<uint64_t> end;
         uint64_t len = 0;
         const uint32_t first = k;
         while (k < n_points && end.size() < ends) {
             uint64_t kmin, kmax;
             const double t0 = e->t_now;
-            int rc = schedule_ensemble(e, t_grid[k], s, &kmin, &kmax);
-            if (rc) return rc;
+            refused = schedule_ensemble(e, t_grid[k], s, &kmin, &kmax);
+            if (refused) break;
             if (len + kmax > cap) {
                 if (!end.empty()) {  // the next launch draws and takes this point
                     e->t_now = t0;
@@ -1314,7 +1316,7 @@ static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, co
                     break;
                 }
                 note_scheduled(e, kmin, kmax);
-                rc = run_shared(e, 0, s);
+                const int rc = run_shared(e, 0, s);
                 if (rc) return rc;
                 kmax = 0;
             }
@@ -1322,6 +1324,11 @@ static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, co
             end.push_back(len);
             ++k;
         }
+        if (end.empty()) break;
+        // an index past the last replica reads -1
+        if (what.rec_n_sel)
+            HIP_TRY(launch_fill_i32(what.rec_out + 3ull * first * what.rec_n_sel,
+                                    3ull * what.rec_n_sel * end.size(), -1, s));
         for (size_t i = 0; i < end.size(); i += kRecEnds) {
             RecEnds v{};
             const int n = (int)std::min<size_t>(kRecEnds, end.size() - i);
@@ -1343,7 +1350,7 @@ static int record_shared(bwg_ens *e, const double *t_grid, uint32_t n_points, co
         if (rc) return rc;
         e->zE += len;
     }
-    return BWG_OK;
+    return refused;
 }
 
 extern "C" int bwg_ensemble_record(bwg_ens *e, const double *t_grid, uint32_t n_points,
@@ -1370,8 +1377,6 @@ extern "C" int bwg_ensemble_record(bwg_ens *e, const double *t_grid, uint32_t n_
     // every wave looks through the selection once (1024 entries: a few us)
     if (e->zs && e->engine == BWG_ENGINE_BITWISE && e->word_bits == 32 && !e->epl && n_points &&
         n_sel <= 1024 && !e->pending && e->table_cap >= 8) {
-        // an index past the last replica reads -1
-        if (n_sel) HIP_TRY(launch_fill_i32(dev_out, 3ull * n_sel * n_points, -1, s));
         WmArgs what{};
         what.rec_sel = dev_sel;
         what.rec_out = dev_out;

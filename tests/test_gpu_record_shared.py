@@ -109,3 +109,35 @@ def test_checkpoint_of_a_recorded_ensemble(torch):
         x.advance(0.6)
     np.testing.assert_array_equal(a.read_counts().cpu().numpy(), b.read_counts().cpu().numpy())
     np.testing.assert_array_equal(a.read_events()[0].cpu().numpy(), b.read_events()[0].cpu().numpy())
+
+
+# the last point's mean is refused: in a launch of its own, and (8 entries)
+# after points that earlier launches took
+@pytest.mark.parametrize("cap", [0, 8])
+@pytest.mark.parametrize("n", [0, 1, 7])
+def test_a_refused_point_leaves_the_points_before_it(torch, n, cap):
+    """The points before one that fails are run and recorded, and the ensemble
+    stands at the last of them."""
+    net = paper_network(16)
+    M = 200
+    e = bwg.Ensemble(bwg.Network(net), M, seed=3, net_id=5, shared_threshold=True,
+                     table_capacity=cap)
+    o = ssa.OracleEnsemble(net, M, seed=3, net_id=5, draw=ssa.DRAW_SHARED)
+    for x in (e, o):
+        x.init(("multinomial",))
+        x.advance(0.01)
+    with pytest.raises(bwg.BwgError):
+        e.record(GRID[:n] + [float("inf")], [0, 199], threshold=9)
+    for t in GRID[:n]:
+        o.advance(t)
+    for more in (0, 50):
+        e.step(more)
+        o.step(more)
+        s = e.stats()
+        assert s["t_now"] == ([0.01] + GRID)[n] and s["advance_index"] == n + 1
+        assert e.pending() == 0
+        np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
+        np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
+    e.advance(2.0)
+    o.advance(2.0)
+    np.testing.assert_array_equal(e.read_counts().cpu().numpy(), o.counts)
