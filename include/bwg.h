@@ -520,7 +520,8 @@ void bwg_ensemble_destroy(bwg_ens *ens);
 typedef struct bwg_batch bwg_batch;
 
 typedef struct {
-    int32_t waves;          /* persistent grid in wavefronts, 0 = default (2048)  */
+    int32_t waves;          /* persistent grid in wavefronts, 0 = default (2048,
+                               or 4096 where every member runs the lanes loop)  */
     int32_t order;          /* 0: longest pending work first, 1: member order     */
     int32_t max_ensembles;  /* capacity for later member changes (0: initial n)   */
     int32_t reserved0;

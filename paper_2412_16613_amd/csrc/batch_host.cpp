@@ -20,7 +20,7 @@ struct bwg_batch {
     std::vector<int> bucket;       // persistent-kernel plane bucket per member
     std::vector<double> cost;      // issue cost of one event of a 64-word item, per member
     std::vector<double> lane_cost; // the same for a 2-word lanes item
-    int waves = 0;
+    int waves = 0;                 // persistent grid (0: the kernel's default)
     int order = 0;
     int cap_ens = 0;
     uint64_t cap_items = 0;
@@ -245,7 +245,7 @@ extern "C" int bwg_batch_create(bwg_ens *const *ens, int32_t n, void *dev_buf, u
         return fail(BWG_ENOMEM, "batch buffer of %llu bytes, need %llu",
                     (unsigned long long)buf_bytes, (unsigned long long)need);
     auto b = new bwg_batch();
-    b->waves = (opts && opts->waves > 0) ? opts->waves : 2048;
+    b->waves = (opts && opts->waves > 0) ? opts->waves : 0;
     b->order = opts ? opts->order : 0;
     b->cap_ens = cap_ens;
     b->cap_items = cap_items;
@@ -427,15 +427,16 @@ static int enqueue_pass(bwg_batch *b, uint64_t max_events, hipStream_t s)
 {
     if (!b->n_items) return BWG_OK;
     HIP_TRY(launch_batch_prologue(b->d_counter, s));
+    // a grid that was asked for is kept; the defaults fill the chip: four waves
+    // of the lanes kernel fit a SIMD where two of the word kernel's do
     if (b->all_lanes) {
-        // four of its waves fit a SIMD where two of the word kernel's do
         HIP_TRY(launch_persistent_lanes(b->d_ens, b->d_items, (uint32_t)b->n_pairs,
                                         (uint32_t)(b->n_items - b->n_pairs), b->d_counter,
-                                        b->waves * 2, max_events, s));
+                                        b->waves ? b->waves : 4096, max_events, s));
         return BWG_OK;
     }
-    HIP_TRY(launch_persistent(b->d_ens, b->d_items, (uint32_t)b->n_items, b->d_counter, b->waves,
-                              max_events, b->lanes_items, s));
+    HIP_TRY(launch_persistent(b->d_ens, b->d_items, (uint32_t)b->n_items, b->d_counter,
+                              b->waves ? b->waves : 2048, max_events, b->lanes_items, s));
     return BWG_OK;
 }
 

@@ -47,7 +47,7 @@ import paper_2412_16613_amd as bwg
 
 class Server:
     def __init__(self, hbm_budget=64 << 30, chunk=4096, max_members=1024,
-                 max_items=1 << 19, waves=2048, n_bins=256, keep_counts=False,
+                 max_items=1 << 19, waves=0, n_bins=256, keep_counts=False,
                  lattice_chunk=1 << 17, depth=2, lanes_events=0, lattice_streams=3,
                  device="cuda", log=None):
         import torch

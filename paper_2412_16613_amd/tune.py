@@ -34,7 +34,7 @@ import time
 CACHE = os.environ.get("BWG_TUNE_CACHE",
                        os.path.join(os.path.dirname(os.path.abspath(__file__)),
                                     "tune_cache.json"))
-GRIDS = [(w, o) for w in (1024, 2048, 3072, 4096) for o in (0,)] + [(2048, 1)]
+GRIDS = [(w, 0) for w in (1024, 2048, 3072, 4096)] + [(0, 1)]     # against (0, 0): the default
 TOP_K = [0, 2, 4, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256]
 
 
@@ -91,7 +91,8 @@ def _time(bwg, torch, items, nets, waves, order, lanes, horizon_scale, device):
 
 
 def tune(items, horizon_scale=0.1, device="cuda", force=False):
-    """Return dict(waves, order, lanes, timings) for a batch described by items."""
+    """Return dict(waves, order, lanes, timings) for a batch described by items
+    (waves 0: the batch's default grid)."""
     import torch
     import paper_2412_16613_amd as bwg
     key = signature(items)
@@ -103,22 +104,20 @@ def tune(items, horizon_scale=0.1, device="cuda", force=False):
     timings = {}
     best = None
     by_chain = chain_order(items, quantized)
-    _time(bwg, torch, items, nets, 2048, 0, set(), horizon_scale, device)   # warm caches
+    _time(bwg, torch, items, nets, 0, 0, set(), horizon_scale, device)   # warm caches
     for k in TOP_K:
         if k > len(items):
             k = len(items)
         lanes = sorted(by_chain[:k])
-        if "lanes=%d/2048/0" % k in timings:
+        if "lanes=%d/0/0" % k in timings:
             break
-        dt = _time(bwg, torch, items, nets, 2048, 0, set(lanes), horizon_scale, device)
-        timings["lanes=%d/2048/0" % k] = dt
+        dt = _time(bwg, torch, items, nets, 0, 0, set(lanes), horizon_scale, device)
+        timings["lanes=%d/0/0" % k] = dt
         if best is None or dt < best[0]:
             best = (dt, lanes)
     lanes = best[1]
-    choice = (best[0], 2048, 0)
+    choice = (best[0], 0, 0)
     for waves, order in GRIDS:
-        if (waves, order) == (2048, 0):
-            continue
         dt = _time(bwg, torch, items, nets, waves, order, set(lanes), horizon_scale, device)
         timings["%d/%d" % (waves, order)] = dt
         if dt < choice[0]:

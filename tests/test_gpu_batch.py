@@ -99,6 +99,32 @@ def test_queue_order_and_grid_do_not_change_results(torch, waves, order):
     _assert_same(_state(torch, ref), _state(torch, other))
 
 
+def test_a_grid_asked_for_is_kept(torch):
+    """One wavefront takes the pairs of words of a batch on the lanes loop one
+    after another, two wavefronts take two at a time: equal chains, so half
+    the time."""
+    _say("case grid in time")
+    net = bwg.Network(frank_network(1024, k0=0.1))
+    e = bwg.Ensemble(net, 128, seed=1)          # four words, two pairs
+    ms = {}
+    for waves in (1, 2):
+        b = bwg.Batch([e], waves=waves)
+        runs = []
+        for _ in range(4):
+            e.init_fixed((0, 0, 1024))
+            torch.cuda.synchronize()
+            start = torch.cuda.Event(enable_timing=True)
+            stop = torch.cuda.Event(enable_timing=True)
+            start.record()
+            b.advance([40000 / net.quantized()["Lambda"]])
+            stop.record()
+            torch.cuda.synchronize()
+            runs.append(start.elapsed_time(stop))
+        ms[waves] = min(runs)
+    print("ms", ms, flush=True)
+    assert ms[1] > 1.5 * ms[2]
+
+
 def test_graph_replays_equal_sequential_advances(torch):
     _say("case graph")
     s = torch.cuda.Stream()
