@@ -86,23 +86,42 @@ static uint64_t n_items_of(const bwg_ens *e)
     return (split + 63) / 64 + (words - split + 1) / 2;
 }
 
-// Whether every word of the batch runs the lanes loop.  The word functions of
-// the persistent kernel take shifts and weights at run time (1.8 times the
-// compiled kernels' instructions) and hold a whole chain in one lane: 24
-// uneven networks take 180 ms on them and 17 on the lanes loop, the 256 of the
-// uneven batch 1.5 s (0.43 with the long chains picked for lanes items) and
-// 0.22, 40 small networks of 200000 replicas 5.1 and 5.0 ms.  Only members
-// that were given a word width, or that fill the chip with words by
-// themselves (65536 of them), keep the batch on the word functions.
-static bool batch_on_lanes(bwg_ens *const *ens, size_t n)
+// Whether every word of the batch runs the lanes loop in its next pass (of at
+// most max_events of each member's pending events; 0: all).  The word functions
+// of the persistent kernel hold a whole chain in one lane, so a pass on them
+// lasts as long as its longest chain unless there are words enough to fill the
+// chip: 24 uneven networks take 180 ms on them and 17 on the lanes loop, the
+// 256 of the uneven batch 1.5 s (0.43 with the long chains picked for lanes
+// items) and 0.22.  Where words do fill it, the lanes loop is the slower one
+// while replicas are active: 8 x 2^20 replicas from an all-A start, 300 events
+// each, words against lanes: N_tot = 16 2.25 / 2.27 ms, 32 2.71 / 4.31, 128 2.99
+// / 4.00, 1024 (k0 = 0.1, 5000 events) 38.8 / 52.8; 8 x 2^18: 1.20 / 0.82, 1.38
+// / 1.31, 1.53 / 1.25, 19.4 / 13.8.  The two estimates below, in the units of the
+// members' costs, choose the faster one in all 60 batches of equal members
+// measured so (N_tot 16 to 4000, 4 to 32 x 2^18 replicas, 300 to 5000 events) in
+// which the lanes loop loses; uneven batches lie far from the line.  Members
+// that were given a word width keep their words, as do those that fill the chip
+// with words by themselves (65536 of them).
+static bool batch_on_lanes(const bwg_batch *b, uint64_t max_events)
 {
     uint64_t pairs = 0;
-    for (size_t k = 0; k < n; ++k) {
-        const uint64_t words = (ens[k]->M + 31) / 32;
-        if (ens[k]->keep_words || words > 65536) return false;
-        pairs += (words + 63) / 64 * 32;
+    bool asked = true;  // every member on lanes items already
+    double lanes = 0, items = 0, chain = 0;
+    for (size_t k = 0; k < b->ens.size(); ++k) {
+        const bwg_ens *e = b->ens[k];
+        const uint64_t words = (e->M + 31) / 32, groups = (words + 63) / 64;
+        pairs += groups * 32;
+        if (lanes_split(e) == 0) continue;
+        asked = false;
+        if (e->keep_words || words > 65536) return false;
+        const double ev =
+            (double)(max_events ? std::min(max_events, e->pending) : e->pending);
+        lanes += (double)words * ev * b->lane_cost[k];
+        items += (double)groups * ev * b->cost[k];
+        chain = std::max(chain, ev * b->cost[k]);
     }
-    return pairs < (1ull << 31);
+    if (pairs >= (1ull << 31)) return false;
+    return asked || lanes / 9000 <= std::max(chain, items / 2000);
 }
 
 static uint64_t layout_bytes(int n, uint64_t items, uint64_t *off_ens, uint64_t *off_budget,
@@ -284,12 +303,12 @@ extern "C" void bwg_batch_destroy(bwg_batch *b) { delete b; }
 
 // Queue of the members' items, longest pending work first (or in member
 // order), uploaded on the stream.
-static int stage_items(bwg_batch *b, hipStream_t s)
+static int stage_items(bwg_batch *b, uint64_t max_events, hipStream_t s)
 {
     std::vector<std::pair<double, BatchItem>> q;
     q.reserve(b->n_items);
     b->lanes_items = false;
-    b->all_lanes = batch_on_lanes(b->ens.data(), b->ens.size());
+    b->all_lanes = batch_on_lanes(b, max_events);
     b->n_pairs = 0;
     for (size_t k = 0; k < b->ens.size(); ++k) {
         const bwg_ens *e = b->ens[k];
@@ -463,7 +482,7 @@ extern "C" int bwg_batch_advance(bwg_batch *b, const double *t_end, void *stream
     rc = enqueue_budgets(b, s);
     if (rc) return rc;
     note_budgets(b, t_end, kmin, kmax);
-    rc = stage_items(b, s);
+    rc = stage_items(b, 0, s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(b->staged, s));
     b->staged_pending = true;
@@ -479,7 +498,7 @@ extern "C" int bwg_batch_run(bwg_batch *b, uint64_t max_events, void *stream)
     if (!b) return fail(BWG_EINVAL, "null batch");
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(sync_staging(b));
-    int rc = stage_items(b, s);
+    int rc = stage_items(b, max_events, s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(b->staged, s));
     b->staged_pending = true;
@@ -516,7 +535,7 @@ extern "C" int bwg_batch_graph_advance(bwg_batch *b, double dt, int32_t n_steps,
     if (rc) return rc;
     // the queue order of the first step serves every replay
     for (size_t k = 0; k < n; ++k) b->ens[k]->pending = b->ens[k]->lag + kmax[k];
-    rc = stage_items(b, s);
+    rc = stage_items(b, 0, s);
     if (rc) return rc;
     HIP_TRY(hipEventRecord(b->staged, s));
     b->staged_pending = true;

@@ -125,6 +125,47 @@ def test_a_grid_asked_for_is_kept(torch):
     assert ms[1] > 1.5 * ms[2]
 
 
+def test_members_that_fill_the_chip_with_words(torch):
+    """Active replicas enough for every SIMD: the batch stays on the word
+    functions, whose results are the lanes loop's, and does not take longer
+    than one that was asked for words (it took 1.6 times as long on the lanes
+    loop)."""
+    _say("case full chip")
+    net = bwg.Network(frank_network(32))
+    n, t = 8, 300 / net.quantized()["Lambda"]
+    ms, got = {}, {}
+    for kw in (0, 32):
+        ens = [bwg.Ensemble(net, (1 << 20) - 5 * k, seed=3, net_id=k, word_bits=kw)
+               for k in range(n)]
+        b = bwg.Batch(ens)
+        runs = []
+        for _ in range(4):
+            for e in ens:
+                e.init_fixed((0, 0, 32))
+            torch.cuda.synchronize()
+            start = torch.cuda.Event(enable_timing=True)
+            stop = torch.cuda.Event(enable_timing=True)
+            start.record()
+            b.advance([t] * n)
+            stop.record()
+            torch.cuda.synchronize()
+            runs.append(start.elapsed_time(stop))
+        ms[kw] = min(runs)
+        for e in ens:               # a pass of few events, and one that ends it
+            e.schedule(2 * t)
+        b.run(100)
+        b.run()
+        got[kw] = [(e.read_counts(), *e.read_events()) for e in ens]
+    alone = [bwg.Ensemble(net, (1 << 20) - 5 * k, seed=3, net_id=k, engine="lanes")
+             for k in range(n)]
+    for k, e in enumerate(alone):
+        e.init_fixed((0, 0, 32)).advance(t).advance(2 * t)
+        for x, y, z in zip((e.read_counts(), *e.read_events()), got[0][k], got[32][k]):
+            assert bool((x == y).all()) and bool((x == z).all())
+    print("ms", ms, flush=True)
+    assert ms[0] < 1.25 * ms[32]
+
+
 def test_graph_replays_equal_sequential_advances(torch):
     _say("case graph")
     s = torch.cuda.Stream()
