@@ -441,10 +441,9 @@ static int enqueue_budgets(bwg_batch *b, hipStream_t s)
     return BWG_OK;
 }
 
-// One persistent pass over the staged queue (kernels only).
-static int enqueue_pass(bwg_batch *b, uint64_t max_events, hipStream_t s)
+// One persistent launch over the staged queue (kernels only).
+static int enqueue_launch(bwg_batch *b, uint64_t max_events, hipStream_t s)
 {
-    if (!b->n_items) return BWG_OK;
     HIP_TRY(launch_batch_prologue(b->d_counter, s));
     // a grid that was asked for is kept; the defaults fill the chip: four waves
     // of the lanes kernel fit a SIMD where two of the word kernel's do
@@ -457,6 +456,23 @@ static int enqueue_pass(bwg_batch *b, uint64_t max_events, hipStream_t s)
     HIP_TRY(launch_persistent(b->d_ens, b->d_items, (uint32_t)b->n_items, b->d_counter,
                               b->waves ? b->waves : 2048, max_events, b->lanes_items, s));
     return BWG_OK;
+}
+
+// One persistent pass: a launch, but for members with more pending events than
+// the lanes loop runs in one.
+static int enqueue_pass(bwg_batch *b, uint64_t max_events, hipStream_t s)
+{
+    if (!b->n_items) return BWG_OK;
+    uint64_t todo = 0;
+    for (const auto *e : b->ens) todo = std::max(todo, e->pending);
+    if (max_events) todo = std::min(todo, max_events);
+    const bool lanes = b->all_lanes || b->lanes_items;
+    for (; lanes && todo > kLanesEvents; todo -= kLanesEvents) {
+        const int rc = enqueue_launch(b, kLanesEvents, s);
+        if (rc) return rc;
+        if (max_events) max_events -= kLanesEvents;
+    }
+    return enqueue_launch(b, max_events, s);
 }
 
 static void note_budgets(bwg_batch *b, const double *t_end, const std::vector<uint64_t> &kmin,

@@ -151,6 +151,10 @@ extern const int kGenVariantCount;
 
 hipError_t launch_plain(const PlainArgs &a, hipStream_t s, int block);
 hipError_t launch_wm_lanes(const WmArgs &a, hipStream_t s);
+// Events of a replica that one launch of the lanes loop runs at most: a word's
+// real events of a launch are summed in 32 bits (64-bit sums in the loop cost
+// 1 to 2 % of full launches and 5 % of a batch's).
+constexpr uint64_t kLanesEvents = 1ull << 26;
 // n <= kRecEnds values to dst (uint64), passed by value.
 constexpr int kRecEnds = 64;
 struct RecEnds {

@@ -978,8 +978,7 @@ void bwg::note_ran(bwg_ens *e, uint64_t max_events)
 
 // One launch of the pending events of every word, at most max_events each
 // (0: all of them).
-static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s,
-                         const WmArgs *rec = nullptr)
+static int launch_once(bwg_ens *e, uint64_t max_events, hipStream_t s, const WmArgs *rec)
 {
     const bwg_net *n = e->net;
     if (e->engine != BWG_ENGINE_PLAIN) {
@@ -1061,6 +1060,22 @@ static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s,
     return BWG_OK;
 }
 
+// The same in as many launches as the loop's sums need (one, but for chains of
+// more than 2^26 events on the lanes loop).
+static int launch_events(bwg_ens *e, uint64_t max_events, hipStream_t s,
+                         const WmArgs *rec = nullptr)
+{
+    const bool lanes = e->engine == BWG_ENGINE_LANES || words_on_lanes(e) ||
+                       (e->jit && jit_on_lanes(e->jit));
+    uint64_t todo = max_events ? std::min(max_events, e->pending) : e->pending;
+    for (; lanes && todo > kLanesEvents; todo -= kLanesEvents) {
+        const int rc = launch_once(e, kLanesEvents, s, rec);
+        if (rc) return rc;
+        if (max_events) max_events -= kLanesEvents;
+    }
+    return launch_once(e, max_events, s, rec);
+}
+
 // Shared-threshold ensembles move in lockstep (every replica at event zE):
 // run up to max_events (0: all) of the pending events in launches of at most
 // the table's capacity, each preceded by the fill of its thresholds.
@@ -1070,6 +1085,7 @@ static int run_shared(bwg_ens *e, uint64_t max_events, hipStream_t s)
     if (max_events && max_events < todo) todo = max_events;
     uint64_t cap = e->table_cap * 2;  // uint32 thresholds in the table region
     if (e->epl && e->epl < cap) cap = e->epl;
+    if (e->engine == BWG_ENGINE_LANES) cap = std::min(cap, kLanesEvents);
     while (todo) {
         const uint64_t len = todo < cap ? todo : cap;
         HIP_TRY(launch_shared_fill((uint32_t *)e->table, e->zE, len, e->seed, e->net_id, e->zs,

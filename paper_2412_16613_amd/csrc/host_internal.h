@@ -39,6 +39,8 @@ struct TraceRange {
 struct JitKernel;
 void jit_release(JitKernel *k);
 hipError_t jit_launch(const JitKernel *k, const WmArgs &a, hipStream_t s);
+// Whether it is a lanes kernel (at most kLanesEvents a launch).
+bool jit_on_lanes(const JitKernel *k);
 
 }  // namespace bwg
 

@@ -703,6 +703,8 @@ int jit_build_codes(bwg_net *n, bool general, bool frank)
     return rc;
 }
 
+bool jit_on_lanes(const JitKernel *k) { return k->lanes != nullptr; }
+
 hipError_t jit_launch(const JitKernel *k, const WmArgs &a, hipStream_t s)
 {
     WmArgs arg = a;

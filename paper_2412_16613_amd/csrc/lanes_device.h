@@ -243,7 +243,7 @@ __device__ __forceinline__ void unpack_counts(const WmArgs &a, uint64_t w, int l
 template <int S>
 __device__ __forceinline__ void pack_counts(const WmArgs &a, uint64_t w, int l, int hv,
                                             const LaneWindow &v, const uint32_t (&N)[S],
-                                            uint64_t nreal)
+                                            uint32_t nreal)
 {
     const int nbm = a.nb_mem;
     const bool valid = w < a.n_words;
@@ -315,14 +315,13 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
         return n >> SH;
     };
     const uint64_t Ts = v.mine ? (v.T0 < v.hi ? v.T0 : v.hi) : 0;
-    uint64_t sum0 = 0, sum1 = 0;  // real events of the wave's two words
-    // runs of events that share their index's bits 26 and up: the draws need
-    // that of bits 32 and up, and a run's real events fit 32 bits (32 replicas
-    // times 2^26), where a launch's need not
+    // real events of the wave's two words: a launch runs at most kLanesEvents
+    // of a replica, so that 32 bits hold them
+    uint32_t real0 = 0, real1 = 0;
+    // runs of events that share their index's bits 32 and up
     bool done = false;
     for (uint64_t base = v.lo; !done && wave_any(base < v.hi);) {
-        const uint64_t room = (base | 0x3FFFFFFull) + 1;
-        uint32_t real0 = 0, real1 = 0;
+        const uint64_t room = (base | 0x3FFFFFFFull) + 1;
         const uint64_t stop = v.hi < room ? v.hi : room;
         const uint32_t span = base < stop ? (uint32_t)(stop - base) : 0u;
         // this replica's events of the run: [from, to)
@@ -387,10 +386,6 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
                     const uint64_t fired = rep.fire(n, on, onm);
                     real0 += (uint32_t)__builtin_popcount((uint32_t)fired);
                     real1 += (uint32_t)__builtin_popcount((uint32_t)(fired >> 32));
-                    // added by the vector unit where a SIMD holds a wave or
-                    // two (517 words, N_tot = 3535, 20000 events: 1.97 ms,
-                    // 2.12 with scalar additions, which win on full SIMDs)
-                    if constexpr (PAIR) asm("" : "+v"(real0), "+v"(real1));
                     onm = ballot(cm != 0) & ballot(rep.total() <= bound);
 #if __has_builtin(__builtin_amdgcn_inverse_ballot_w64)
                     // the mask itself, which the ballots have formed
@@ -447,13 +442,11 @@ __device__ __forceinline__ void wm_lanes(const WmArgs &a, uint64_t w, uint32_t *
             }
         }
         base = base < stop ? stop : base;
-        sum0 += real0;
-        sum1 += real1;
     }
     if (draws) return;
     uint32_t N[Replica::S];
     rep.get_counts(N);
-    pack_counts(a, valid ? w : ~0ull, l, hv, v, N, hv ? sum1 : sum0);
+    pack_counts(a, valid ? w : ~0ull, l, hv, v, N, hv ? real1 : real0);
 }
 
 // The same for shared thresholds: at every event all replicas compare the n
@@ -470,15 +463,13 @@ __device__ __forceinline__ void wm_lanes_shared(const WmArgs &a, uint64_t w)
     uint32_t N[Replica::S];
     unpack_counts(a, w, l, N);
     rep.set_counts(N);
-    uint64_t nreal = 0;
+    uint32_t nreal = 0;
     for (uint64_t e = a.zbase; e < a.zbase + a.zlen; ++e) {
         const uint32_t n = shared_at(a, e);
         nreal += live && n < rep.total() ? 1u : 0u;
         rep.fire(n, live, 0);
     }
-    for (int o = 16; o; o >>= 1)
-        nreal += (uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)nreal, o, 32) |
-                 ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(nreal >> 32), o, 32) << 32);
+    for (int o = 16; o; o >>= 1) nreal += (uint32_t)__shfl_xor((int)nreal, o, 32);
     rep.get_counts(N);
     pack_counts(a, w, l, hv, v, N, nreal);
 }

@@ -331,6 +331,34 @@ def test_real_events_of_one_launch_past_32_bits(torch):
     assert (c[:, 0] + c[:, 1] == 2).all() and (c >= 0).all()
 
 
+@pytest.mark.parametrize("M", [64, 100000])
+@pytest.mark.parametrize("call", ["step", "run", "batch"])
+def test_chains_of_several_launches(torch, call, M):
+    """More events than one launch of the loop runs, nearly all of them after
+    the chains' ends: every event counts."""
+    net = bwg.Network(frank_network(5, k0=0.3))
+    n = 3 * (1 << 26) + 7
+    a, b = (bwg.Ensemble(net, M, seed=3, engine="lanes", table_capacity=1 << 19)
+            .init_fixed((0, 0, 5)) for _ in range(2))
+    b.step(20000)
+    if call == "step":
+        a.step(n)
+    else:
+        a.schedule(n / net.quantized()["Lambda"])
+        runs = bwg.Batch([a]) if call == "batch" else a
+        runs.run(100)
+        runs.run(2 * (1 << 26) + 5)
+        runs.run()
+    assert a.pending() == 0
+    ev, real = a.read_events()
+    if call == "step":
+        assert bool((ev == n).all())
+    else:
+        assert n - 10 ** 6 < int(ev.min()) < int(ev.max()) < n + 10 ** 6
+    np.testing.assert_array_equal(a.read_counts().cpu().numpy(), b.read_counts().cpu().numpy())
+    np.testing.assert_array_equal(real.cpu().numpy(), b.read_events()[1].cpu().numpy())
+
+
 # ---- states that nothing leaves -----------------------------------------------------
 
 @pytest.mark.parametrize("kw", [dict(engine="lanes"), dict(word_bits=32), dict(block=256),
