@@ -646,20 +646,26 @@ static bool lanes_fit(const bwg_net *n)
 // same draws and results) instead of its word kernels.  A word's events are
 // one long chain, so up to one wave per SIMD (65536 words) a bit-sliced launch
 // takes the same time whatever its size, while the lanes loop's time falls
-// with the words.  Per 1000 events at 2^20 replicas (32768 words), words
-// against lanes: N_tot = 1024 1.09 against 0.65 to 0.89 ms (7 and 39 % of the
-// events real), N_tot = 32 0.70 against 0.52 ms (2 % real) or 1.15 ms (9 %);
-// at 2^19 replicas 1.09 against 0.36 to 0.49 and 0.70 against 0.29 or 0.66 ms.
-// The lines lie where the lanes loop still wins when most events are real: at
-// 49152 words from 10 count planes on (1.62 ms for one wave per word against
-// 0.97 to 1.32), at 24576 below.  An explicit block size or word width keeps
-// the word kernels, and shared thresholds (no draws per word) always do.
+// with the words, and with the share of events that are real.  The lines lie
+// where the lanes loop is no slower than the words in an ensemble's active
+// phase (all-A start; lanes / words, ms; both gain once replicas have ended,
+// the lanes loop more).  300 events: N_tot = 32 at 16384 words 0.26 / 0.27, at
+// 20480 0.30 / 0.27, at 24576 0.36 / 0.28; N_tot = 100 at 20480 0.25 / 0.25, at
+// 24576 0.29 / 0.25; N_tot = 500, k0 = 0.1, at 24576 0.28 / 0.32.  From 10
+// planes on a word takes 1.09 ms per 1000 events up to 32768 words and twice
+// that past half a wave per SIMD, where the two waves of a word no longer fit:
+// the line lies at 49152, though there the longest active phases lose
+// (N_tot = 1024, k0 = 0.01: 2000 events 2.35 / 2.95, 10000 14.3 / 14.4; k0 = 0.1:
+// 3.27 / 3.07 and 16.0 / 15.2, but 28.2 / 53.9 for 40000).  An explicit block
+// size or word width keeps the word kernels, and shared thresholds (no draws
+// per word) always do.
 static bool words_on_lanes(const bwg_ens *e)
 {
     if (e->engine != BWG_ENGINE_BITWISE || e->lat || e->zs || e->block > 0 || e->keep_words ||
         e->gvar || e->jit || !lanes_fit(e->net))
         return false;
-    return (e->M + 31) / 32 <= (e->net->q.b >= 10 ? 49152u : 24576u);
+    const int b = e->net->q.b;
+    return (e->M + 31) / 32 <= (b >= 10 ? 49152u : b >= 8 ? 24576u : b == 7 ? 20480u : 16384u);
 }
 
 // Whether a general ensemble of this many words runs the lanes kernel compiled

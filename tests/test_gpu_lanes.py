@@ -210,7 +210,8 @@ def test_word_kernels_of_small_ensembles(torch, net, init):
     np.testing.assert_array_equal(e.read_events()[0].cpu().numpy().astype(np.uint64), o.E)
 
 
-@pytest.mark.parametrize("n_tot,words", [(32, 24576), (1024, 49152)])
+@pytest.mark.parametrize("n_tot,words", [(32, 16384), (100, 20480), (32, 24576), (200, 24576),
+                                         (1024, 49152)])
 @pytest.mark.parametrize("more", [0, 1])
 def test_both_sides_of_the_size_rule(torch, n_tot, words, more):
     """Around the size at which the default leaves the lanes loop, every
@@ -225,6 +226,32 @@ def test_both_sides_of_the_size_rule(torch, n_tot, words, more):
     for g in got[1:]:
         for x, y in zip(g, got[0]):
             assert bool((x == y).all())
+
+
+def active_ms(torch, net, M, start, events, **kw):
+    e = bwg.Ensemble(net, M, seed=3, **kw)
+    ms = []
+    for _ in range(6):
+        e.init_fixed(start)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda.synchronize()
+        a.record()
+        e.step(events)
+        b.record()
+        torch.cuda.synchronize()
+        ms.append(a.elapsed_time(b))
+    return min(ms)
+
+
+@pytest.mark.parametrize("n_tot,k0", [(24, 0.1), (32, 0.01), (61, 0.05), (64, 0.01)])
+def test_active_ensembles_keep_the_words_where_they_win(torch, n_tot, k0):
+    """24576 words of few planes, every replica in its active phase (the lanes
+    loop takes 1.2 to 1.3 times as long)."""
+    net = bwg.Network(frank_network(n_tot, k0=k0))
+    M, start = 32 * 24576, (0, 0, n_tot)
+    got, words = (active_ms(torch, net, M, start, 200, **kw) for kw in ({}, dict(word_bits=32)))
+    print("ms", n_tot, k0, got, words, flush=True)
+    assert got < 1.12 * words
 
 
 @pytest.mark.parametrize("word_bits", [0, 32], ids=["lanes", "words"])
