@@ -670,20 +670,25 @@ static bool words_on_lanes(const bwg_ens *e)
 
 // Whether a general ensemble of this many words runs the lanes kernel compiled
 // for the network or its word kernels.  A word's event costs a shifted
-// subtraction per set bit of every weight (two instructions a plane) and
-// updates every replica, the lanes loop's a multiply-add per reaction for the
-// replicas with a real event.  Per 200 events, words against lanes: 12
-// reactions with 67 set bits 1.47 against 0.16 ms at 2^19 replicas, 2.45
-// against 1.13 at 2^22; 5 reactions with 24 set bits 0.60 / 0.14 and 1.08 /
-// 0.97 ms; 3 reactions with 5 set bits 0.22 / 0.08 and 0.53 / 0.50 ms; one
-// reaction with one set bit (81 % of the events real) 0.13 / 0.09 at 2^19 and
-// 0.14 / 0.16 at 2^20.
+// subtraction per set bit of every weight, two instructions a plane, and
+// updates every replica; the lanes loop's costs a multiply-add per reaction for
+// the replicas with a real event.  The lines lie where the lanes loop is no
+// slower with every event real, by the set bits times the threshold planes.
+// Lanes / words, ms, 150 events, all of them real: 3 reactions, 3 bits x 6
+// planes 0.12 / 0.09 at 24576 words, 15 x 11 0.14 / 0.17 there and 0.33 / 0.24 at
+// 65536; 6 reactions, 24 x 11 0.21 / 0.23 at 32768, 0.39 / 0.30 at 65536; 30 x 14
+// 0.39 / 0.39 at 65536; 36 x 13 0.56 / 0.64 at 98304, 0.75 / 0.70 at 131072; 48 x
+// 15 1.51 / 1.60 at 262144.  Random networks of 3 to 12 reactions, 5 to 30 % of
+// 100 events real: 8 x 21 0.12 / 0.14 at 32768, 11 x 24 0.31 / 0.29 at 65536, 34 x
+// 30 0.45 / 0.88 and 75 x 29 0.91 / 1.60 at 131072.
 static bool general_on_lanes(const bwg_net *n, uint64_t words)
 {
     if (!jit_lanes_fits(n)) return false;
     int bits = 0;
     for (int j = 0; j < n->R; ++j) bits += __builtin_popcountll((uint64_t)n->q.c[j]);
-    return words <= (bits >= 32 ? ~0ull : (bits >= 4 ? 65536u : 24576u));
+    const int work = bits * n->q.B;
+    if (bits >= 32 && work >= 400) return work >= 640 || words <= 98304;
+    return words <= (work >= 400 ? 65536u : work >= 250 ? 32768u : work >= 100 ? 24576u : 16384u);
 }
 
 extern "C" int bwg_ensemble_state_bytes(const bwg_net *n, uint64_t M, const bwg_opts *o,

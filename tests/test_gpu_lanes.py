@@ -386,6 +386,36 @@ def test_chains_of_several_launches(torch, call, M):
     np.testing.assert_array_equal(real.cpu().numpy(), b.read_events()[1].cpu().numpy())
 
 
+@pytest.mark.parametrize("turned,weight,words", [(3, 163, 65536), (3, 31, 49152), (6, 15, 65536)])
+def test_active_general_networks_keep_the_words_where_they_win(torch, turned, weight, words):
+    """Conversions among three species, every event real (the lanes loop takes
+    1.1 to 1.3 times as long)."""
+    turns = [((1, 0, 0), (0, 1, 0)), ((0, 1, 0), (0, 0, 1)), ((0, 0, 1), (1, 0, 0)),
+             ((1, 0, 0), (0, 0, 1)), ((0, 0, 1), (0, 1, 0)), ((0, 1, 0), (1, 0, 0))][:turned]
+    net = bwg.Network(table(3, turns, [weight] * turned, 100))
+    got, of_words = (active_ms(torch, net, 32 * words, (33, 33, 34), 150, **kw)
+                     for kw in ({}, dict(word_bits=32)))
+    print("ms", turned, weight, words, got, of_words, flush=True)
+    assert got < 1.07 * of_words
+
+
+# both sides of the lines by weight bits times planes
+@pytest.mark.parametrize("weight,turns,words", [(31, 3, 24576), (15, 6, 32768), (117, 6, 65536),
+                                                (63, 6, 98304)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_both_sides_of_the_general_rule(torch, weight, turns, words, more):
+    M = 32 * words + more
+    ring = [((1, 0, 0), (0, 1, 0)), ((0, 1, 0), (0, 0, 1)), ((0, 0, 1), (1, 0, 0)),
+            ((1, 0, 0), (0, 0, 1)), ((0, 0, 1), (0, 1, 0)), ((0, 1, 0), (1, 0, 0))][:turns]
+    net = bwg.Network(table(3, ring, [weight] * turns, 60))
+    got = []
+    for kw in (dict(), dict(word_bits=32)):
+        e = bwg.Ensemble(net, M, seed=2, **kw).init_fixed((20, 20, 20)).step(40)
+        got.append((e.read_counts(), *e.read_events()))
+    for x, y in zip(*got):
+        assert bool((x == y).all())
+
+
 # ---- states that nothing leaves -----------------------------------------------------
 
 @pytest.mark.parametrize("kw", [dict(engine="lanes"), dict(word_bits=32), dict(block=256),
