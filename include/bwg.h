@@ -202,9 +202,9 @@ typedef struct {
  * run the kernel that keeps the planes of the first BWG_LAT_STAGE_SITES sites
  * of each word in LDS for the whole launch (copied in at the start and back at
  * the end), and smaller ensembles, on lattices whose sites all fit beside the
- * schedule (1984 sites with those weights, 832 with others), a kernel that keeps
- * every site there; the results are the same either way.  Ignored for
- * well-mixed networks. */
+ * schedule (1984 sites with those weights, 576 with others, 400 where their
+ * thresholds take 19 planes and more), a kernel that keeps every site there; the
+ * results are the same either way.  Ignored for well-mixed networks. */
 #define BWG_OPT_NO_LDS_STAGE 16u
 #define BWG_LAT_STAGE_SITES 840
 /* Lattice schedule geometry: the component events of a group of 2048

@@ -215,11 +215,19 @@ constexpr int LAT_NCB = 32;
 // Sites up to which one workgroup holds a word's sites in LDS, beside a chunk's
 // schedule: what fits for the weights known at compile time (44 x 44 sites,
 // 1000 replicas, 32768 events: 347 us against 416 in memory; 21 x 17: 444
-// against 866), and for run-time weights, whose selection is long enough to
-// want the memory kernel's threads, where that overtakes (21 x 17: 1335 against
-// 1927; 32 x 32: 961 against 887).
+// against 866).  For weights taken at run time, where the memory kernel, whose
+// 512 threads all take a layer's events, overtakes the one in which one half
+// applies a layer while the other draws: a layer of more events than a half has
+// threads is drawn and applied in turns there, and the longer selection counts
+// twice.  60 events a site of 1000 replicas, one word in LDS / in memory, us:
+// thresholds of up to 18 planes, 24 x 23 sites 970 to 1090 / 1080 to 1190, 24 x 24 990 to 1120 /
+// 1050 to 1130, 25 x 24 1090 to 1230 / 1030 to 1120 (k0 = 0.006 to 0.02; 0.03, a
+// weight of few bits, wins up to 32 x 26); 19 to 23 planes, whose selection
+// holds its planes in scratch, 20 x 20 995 to 1100 / 1035 to 1100, 23 x 20 1075 to
+// 1240 / 1100 to 1155, 28 x 28 1410 to 1930 / 1140 to 1220.
 constexpr int LAT_WORD_SITES = 1984;
-constexpr int LAT_WORD_SITES_RT = 832;
+constexpr int LAT_WORD_SITES_RT19 = 576;
+constexpr int LAT_WORD_SITES_RT24 = 400;
 constexpr int LAT_SLOT = 3 * LAT_CH + 64;   // uint32 per (group, chunk) slot
 constexpr int LAT_MAX_SITES = 4096;
 

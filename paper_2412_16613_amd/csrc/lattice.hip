@@ -1374,8 +1374,8 @@ hipError_t launch_lat_schedule(const LatArgs &a, uint32_t n_groups, hipStream_t 
     X(4, 4, 24, -1, -1, -1, 4, 512, 0) X(5, 4, 24, -1, -1, -1, 1, 512, 0)                      \
     X(6, 4, 19, 246, 2048, 2048, 4, 1024, 4 * BWG_LAT_STAGE_SITES)                             \
     X(7, 4, 19, 246, 2048, 2048, 1, 512, LAT_WORD_SITES)                                   \
-    X(8, 4, 19, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT)                                     \
-    X(9, 4, 24, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT)
+    X(8, 4, 19, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT19)                                   \
+    X(9, 4, 24, -1, -1, -1, 1, 512, LAT_WORD_SITES_RT24)
 
 // grid: the slices of the band's groups, rounded up to a multiple of the 8 XCDs
 #define BWG_LAT_LAUNCH(ID, P_, BC_, CU_, CA_, CI_, WS_, BL_, ST_)                             \
