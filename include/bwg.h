@@ -285,7 +285,9 @@ void bwg_net_destroy(bwg_net *net);
  * Frank family, open networks and other species counts (the general networks
  * Sec. 6 proposes, on the Sec. 4 state); the Frank-family
  * kernel with the network's weights as constants where no precompiled
- * variant has them.  Ensembles created later only load the code (done once
+ * variant has them.  A general network has one kernel for small and one for
+ * large ensembles, both compiled unless every size runs the same one (a word
+ * width asked for compiles the latter when it needs it).  Ensembles created later only load the code (done once
  * per network).  *built (may be NULL) gets BWG_JIT_GENERAL | BWG_JIT_FRANK
  * for the kernels this network uses, 0 when it runs precompiled kernels
  * only or is a lattice.  EUNSUPPORTED if no bit-sliced kernel runs the

@@ -847,7 +847,10 @@ extern "C" int bwg_net_compile(bwg_net *n, uint32_t *built)
     if (rc) return rc;
     bool gen = false, frank = false;
     jit_plan(n, BWG_ENGINE_BITWISE, var, false, true, &gen, &frank);
-    rc = jit_build_codes(n, gen, frank);
+    // on the general path, those that the size rule takes at some size
+    const uint64_t most = 1ull << 27;   // words
+    rc = jit_build_codes(n, gen && !general_on_lanes(n, most), gen && general_on_lanes(n, 1),
+                         frank);
     if (rc) return rc;
     if (built) *built = (gen ? BWG_JIT_GENERAL : 0u) | (frank ? BWG_JIT_FRANK : 0u);
     return BWG_OK;

@@ -173,9 +173,10 @@ bool jit_lanes_fits(const bwg_net *n);
 // and whether the network fits that kernel's template parameters.
 int jit_frank_get(bwg_net *n, const JitKernel **out);
 bool jit_frank_fits(const bwg_net *n);
-// Build, on the host only, the code objects of the general and/or the Frank
-// kernel that are not built yet (later loads reuse them).
-int jit_build_codes(bwg_net *n, bool general, bool frank);
+// Build, on the host only, the code objects of the general path's word and
+// lanes kernels and/or the Frank kernel that are not built yet (later loads
+// reuse them).
+int jit_build_codes(bwg_net *n, bool words, bool lanes, bool frank);
 // Budgets of one advance to t_end (no event launches); *kmin/*kmax bound K.
 int schedule_ensemble(bwg_ens *e, double t_end, hipStream_t s, uint64_t *kmin, uint64_t *kmax);
 // Bookkeeping after budgets with K in [kmin, kmax] were drawn.

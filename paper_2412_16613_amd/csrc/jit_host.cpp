@@ -694,11 +694,11 @@ int jit_frank_get(bwg_net *n, const JitKernel **out)
     return BWG_OK;
 }
 
-int jit_build_codes(bwg_net *n, bool general, bool frank)
+int jit_build_codes(bwg_net *n, bool words, bool lanes, bool frank)
 {
     std::lock_guard<std::mutex> lock(n->mu);
-    int rc = general ? jit_general_code(n) : BWG_OK;
-    if (!rc && general && jit_lanes_fits(n)) rc = jit_lanes_code(n);
+    int rc = words ? jit_general_code(n) : BWG_OK;
+    if (!rc && lanes) rc = jit_lanes_code(n);
     if (!rc && frank) rc = jit_frank_code(n);
     return rc;
 }
