@@ -306,7 +306,12 @@ def main():
         pv = p["events"] * max(1, args.steps // 2) / (p["ms"] / 1e3)
         out["plain_ssa"] = {"value": pv, "unit": "replica-events/s",
                             "ms_per_step": p["ms"] / max(1, args.steps // 2),
-                            "bitwise_over_plain": value / pv}
+                            # the ratio of the times to one result: the comparator
+                            # draws every event, the lanes loop none past the end of
+                            # a wave's replicas; per event drawn beside it
+                            "bitwise_over_plain": value / pv,
+                            "drawn_fraction": 1.0,
+                            "bitwise_over_plain_per_drawn_event": value * drawn / pv}
     # every replica: histogram of the last step's counts by the integer rule
     from oracle import ssa
     hist_ok = bool(np.array_equal(r["hist"].astype(np.uint64),

@@ -451,7 +451,11 @@ __device__ __forceinline__ void wm_word(const WmArgs &a, const uint64_t w)
     constexpr int WD_AL = Sh::WD_AL, WD_QA = Sh::WD_QA, WD_LD = Sh::WD_LD;
     // all BC / 4 quads are in use but for planes of the last one: its draws
     // share their first rounds (3000001 replicas of 61 molecules, 20 planes:
-    // 2303 -> 2202 us)
+    // 2303 -> 2202 us).  Holding the per-word products takes the N_tot = 32
+    // kernel from 126 registers to 169, from four waves a SIMD to two, which
+    // costs nothing where four would be resident (300 events of 2^23, 2^24, 2^25
+    // and 2^26 replicas, ms, before / now: 1.28 / 1.22, 2.16 / 2.07, 3.83 / 3.88,
+    // 7.22 / 7.33)
     constexpr bool DRAWN = EXACT && !SH;
     const bool valid = w < a.n_words;
     WordRecord rec{};
