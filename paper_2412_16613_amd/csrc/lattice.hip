@@ -859,7 +859,10 @@ __device__ __noinline__ uint32_t lanes_at(const uint64_t *sE, const uint64_t *sE
 // lattice at 2^16 replicas takes 3102 us (3344 before, with the run-time
 // selection and copied registers; 3435 with 17 spilled registers, 3847 with
 // the records read a further event ahead); a pass of the 21 x 17 one at 1000
-// replicas 1681 us (2042).
+// replicas 1681 us (2042).  The staged kernel sits on the edge: 126 registers
+// with layer bounds of their own, 128 and two spilled (32 bytes of scratch a
+// lane) since a bound shares its word with the layer's first hop, which
+// lat_word_kernel needs; a pass of the 64 x 64 lattice did not change by it.
 template <int P, int BC, int64_t CU, int64_t CA, int64_t CI, int WS, int BLOCK, int ST>
 __global__ __launch_bounds__(BLOCK, 1) void lat_event_kernel(LatArgs a)
 {
@@ -1239,7 +1242,7 @@ __global__ __launch_bounds__(BLOCK, 1) void lat_word_kernel(LatArgs a)
 // by reading the planes.  Counters meet over the 8 sites of a wave by shuffles
 // and over the waves in LDS, where each (species, replica) picks out its bits.
 // 97 us for the 402 MB of 64 x 64 sites of 2^16 replicas, 4.1 TB/s (450 with a
-// thread per replica).
+// thread per replica), with 71 of the counters' registers spilled.
 constexpr int LAT_TOT_WORDS = 8, LAT_TOT_SUBS = 128;
 constexpr int LAT_TOT_BLOCK = LAT_TOT_WORDS * LAT_TOT_SUBS;
 

@@ -307,4 +307,4 @@ def test_run_time_weights_stay_in_memory_where_that_wins(k0, side):
             runs.append(a.elapsed_time(b))
         ms.append(min(runs))
     print("ms", k0, side, ms, flush=True)
-    assert ms[0] < 1.05 * ms[1]
+    assert ms[0] < 1.1 * ms[1]
