@@ -97,11 +97,17 @@ static uint64_t n_items_of(const bwg_ens *e)
 // each, words against lanes: N_tot = 16 2.25 / 2.27 ms, 32 2.71 / 4.31, 128 2.99
 // / 4.00, 1024 (k0 = 0.1, 5000 events) 38.8 / 52.8; 8 x 2^18: 1.20 / 0.82, 1.38
 // / 1.31, 1.53 / 1.25, 19.4 / 13.8.  The two estimates below, in the units of the
-// members' costs, choose the faster one in all 60 batches of equal members
+// members' costs, choose the faster one in all of 120 batches of equal members
 // measured so (N_tot 16 to 4000, 4 to 32 x 2^18 replicas, 300 to 5000 events) in
-// which the lanes loop loses; uneven batches lie far from the line.  Members
-// that were given a word width keep their words, as do those that fill the chip
-// with words by themselves (65536 of them).
+// which the lanes loop loses; uneven batches lie far from the line.  The lanes
+// loop's cost of an event follows the share of real ones: a Frank network has 2
+// to 6 N_tot of them until no event leaves its state (measured at N_tot = 16 to
+// 4000, k0 = 0.003 to 0.1), at up to three in four events, so a member has few
+// left after some passes, and the server's later passes, most of whose members
+// are there, are the lanes loop's (1200 arrivals/s: 1.45e12 replica-events/s on
+// it alone, 1.31e12 with every event at the active price).  Members that were
+// given a word width keep their words, as do those that fill the chip with words
+// by themselves (65536 of them).
 static bool batch_on_lanes(const bwg_batch *b, uint64_t max_events)
 {
     uint64_t pairs = 0;
@@ -116,7 +122,10 @@ static bool batch_on_lanes(const bwg_batch *b, uint64_t max_events)
         if (e->keep_words || words > 65536) return false;
         const double ev =
             (double)(max_events ? std::min(max_events, e->pending) : e->pending);
-        lanes += (double)words * ev * b->lane_cost[k];
+        const double done = std::max(0.0, e->net->q.lambda * e->t_now - (double)e->pending);
+        const double left = std::max(0.0, 4.0 * (double)e->net->n_tot - 0.5 * done);
+        const double share = ev > 0 ? std::min(0.75, left / ev) : 0.0;
+        lanes += (double)words * ev * b->lane_cost[k] * (0.75 + 0.8 * share);
         items += (double)groups * ev * b->cost[k];
         chain = std::max(chain, ev * b->cost[k]);
     }
