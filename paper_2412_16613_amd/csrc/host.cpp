@@ -675,12 +675,13 @@ static bool words_on_lanes(const bwg_ens *e)
 // the replicas with a real event.  The lines lie where the lanes loop is no
 // slower with every event real, by the set bits times the threshold planes.
 // Lanes / words, ms, 150 events, all of them real: 3 reactions, 3 bits x 6
-// planes 0.12 / 0.09 at 24576 words, 15 x 11 0.14 / 0.17 there and 0.33 / 0.24 at
-// 65536; 6 reactions, 24 x 11 0.21 / 0.23 at 32768, 0.39 / 0.30 at 65536; 30 x 14
-// 0.39 / 0.39 at 65536; 36 x 13 0.56 / 0.64 at 98304, 0.75 / 0.70 at 131072; 48 x
-// 15 1.51 / 1.60 at 262144.  Random networks of 3 to 12 reactions, 5 to 30 % of
-// 100 events real: 8 x 21 0.12 / 0.14 at 32768, 11 x 24 0.31 / 0.29 at 65536, 34 x
-// 30 0.45 / 0.88 and 75 x 29 0.91 / 1.60 at 131072.
+// planes 0.12 / 0.09 at 24576 words, 15 x 11 0.17 / 0.17 at 32768, 0.33 / 0.24 at
+// 65536; 6 reactions, 18 x 10 0.21 / 0.20 and 24 x 11 0.21 / 0.23 at 32768, 0.38 /
+// 0.27 and 0.39 / 0.30 at 65536; 30 x 14 0.39 / 0.39 at 65536; 36 x 13 0.56 / 0.64
+// at 98304, 0.75 / 0.70 at 131072; 48 x 15 1.51 / 1.60 at 262144.  Random networks
+// of 3 to 12 reactions, 5 to 30 % of 100 events real: 8 x 21 0.12 / 0.14 at 32768,
+// 11 x 24 0.31 / 0.29 at 65536, 34 x 30 0.45 / 0.88 and 75 x 29 0.91 / 1.60 at
+// 131072.
 static bool general_on_lanes(const bwg_net *n, uint64_t words)
 {
     if (!jit_lanes_fits(n)) return false;
@@ -688,7 +689,7 @@ static bool general_on_lanes(const bwg_net *n, uint64_t words)
     for (int j = 0; j < n->R; ++j) bits += __builtin_popcountll((uint64_t)n->q.c[j]);
     const int work = bits * n->q.B;
     if (bits >= 32 && work >= 400) return work >= 640 || words <= 98304;
-    return words <= (work >= 400 ? 65536u : work >= 250 ? 32768u : work >= 100 ? 24576u : 16384u);
+    return words <= (work >= 400 ? 65536u : work >= 100 ? 32768u : 16384u);
 }
 
 extern "C" int bwg_ensemble_state_bytes(const bwg_net *n, uint64_t M, const bwg_opts *o,

@@ -400,7 +400,7 @@ def test_active_general_networks_keep_the_words_where_they_win(torch, turned, we
 
 
 # both sides of the lines by weight bits times planes
-@pytest.mark.parametrize("weight,turns,words", [(31, 3, 24576), (15, 6, 32768), (117, 6, 65536),
+@pytest.mark.parametrize("weight,turns,words", [(1, 3, 16384), (31, 3, 32768), (117, 6, 65536),
                                                 (63, 6, 98304)])
 @pytest.mark.parametrize("more", [0, 1])
 def test_both_sides_of_the_general_rule(torch, weight, turns, words, more):
