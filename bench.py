@@ -67,13 +67,13 @@ HBM_PEAK = 8.0e12               # bytes/s, MI355X HBM3E
 # (the factors of a 1 GiB copy), valid only for the sources they were taken on:
 # kernel -> (sha1 prefix of its sources, sources, bytes per launch, summary file).
 CSRC = os.path.join(ROOT, "paper_2412_16613_amd", "csrc")
-_LANES = ("54962d56c23a", ("bitops.h", "event_draw.h", "lanes_device.h", "lanes_kernel.hip",
+_LANES = ("7d9814f96308", ("bitops.h", "event_draw.h", "lanes_device.h", "lanes_kernel.hip",
                            "wm_device.h"))
-_LATTICE = ("a978bfbb7d7a", ("bitops.h", "bwg_internal.h", "event_draw.h", "lattice.hip"))
+_LATTICE = ("aff58a6185dd", ("bitops.h", "bwg_internal.h", "event_draw.h", "lattice.hip"))
 MEASURED_TRAFFIC = {
     "wm_lanes_kernel": _LANES + ((2 * 16982 + 12672) * 1024,
                                  "profiles/wm_lanes_kernel_frank1024_2p20.md"),
-    "lat_event_kernel": _LATTICE + ((2 * 5829760 + 12900400) * 1024,
+    "lat_event_kernel": _LATTICE + ((2 * 5832660 + 12904500) * 1024,
                                     "profiles/lat_event_kernel_lattice64x64_2p16.md"),
 }
 
