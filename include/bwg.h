@@ -221,7 +221,8 @@ typedef struct {
                                     0 (default), 64, 128, 192 or 256 (EINVAL
                                     otherwise)                               */
     uint64_t table_capacity;     /* Poisson-table entries, 0 = default 65536  */
-    uint64_t events_per_launch;  /* 0 = whole advance in one launch           */
+    uint64_t events_per_launch;  /* 0 = whole advance in one launch (the lanes
+                                    loop: one per 2^26 events of a replica)   */
     uint64_t flags;              /* BWG_OPT_*                                 */
     uint64_t word_bits;          /* replicas per thread of the bit-sliced
                                     engine: 32 (a 32-bit word), 16 (half a

@@ -57,11 +57,10 @@ class Server:
         # last line with the summary of each serve call
         self.log = log
         # well-mixed requests expecting at least this many events per replica
-        # run on the lanes engine (one replica per thread: a word's chain of
-        # events an order of magnitude shorter, at about twice the work per
-        # replica-event); 0 (the default: served at 200 arrivals/s it changes
-        # the latencies by a few per cent and costs throughput at saturation)
-        # keeps every request on bit-sliced words
+        # are put on the lanes engine (one replica per thread: a word's chain of
+        # events an order of magnitude shorter, at up to twice the work per
+        # replica-event of active replicas); 0 (the default) leaves the choice
+        # to the batch, which makes it for every pass
         self.lanes_events = float(lanes_events)
         self.device = torch.device(device)
         self.lattice_chunk = int(lattice_chunk)

@@ -17,12 +17,12 @@ word runs its 32 replicas' events one after another at ~750-1200 wave
 instructions per event (one lane per word), while a lanes item draws the
 thresholds of 32 events at once, transposes them in registers and spends
 instructions on the events that can change a state only: ~10 per event for 64
-replicas where most are null, ~40 where half are not.  Members small enough run
-the lanes loop under the bit-sliced engine as well, so the lanes axis matters
-for the large ones.  The candidates move the k longest chains (events per
-replica x cost per event) to lanes, k from 0 to every member; each is timed on
-a tenth of the horizons (both the longest chain and the total work scale with
-it).
+replicas where most are null, ~40 where half are not.  Where the batch itself
+takes the lanes loop for a pass (uneven batches, few members) the lanes axis
+only cuts items smaller; it decides for batches that fill the chip with words.
+The candidates move the k longest chains (events per replica x cost per event)
+to lanes, k from 0 to every member; each is timed on a tenth of the horizons
+(both the longest chain and the total work scale with it).
 """
 
 import hashlib
